@@ -10,80 +10,274 @@ namespace perch {
 
 // ------------------------------------------------------------------ ICP refinement
 
-// Per-iteration ICP sums over the matched pairs (q, c), one component per
-// lane: n, q (3), c (3), q q^T (9, row-major), q c^T (9, row-major).
+// Per-iteration ICP sums over the matched pairs (q, c): n, q (3), c (3),
+// q q^T (9, row-major), q c^T (9, row-major).
 constexpr int kIcpSums = 25;
 // GICP: 21 upper entries of the 6x6 Gauss-Newton matrix, then 6 of its
 // right-hand side, in 64-bit fixed point (times 1024, rounded).
 constexpr int kGicpSums = 27;
 constexpr int kRedSums = 28;
 
-__device__ __forceinline__ long long icp_pick(int a, long long x, long long y, long long z)
+// Sum of a lane value over the wave (exact 64-bit integers; every lane
+// active), in DPP adds: within rows of 16, then across the rows into lane 63.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ long long dpp_add64(long long x)
 {
-    return a == 0 ? x : (a == 1 ? y : z);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)x, CTRL, ROWS, 0xF, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)((unsigned long long)x >> 32), CTRL, ROWS, 0xF, false);
+    return x + (long long)(((unsigned long long)(uint32_t)hi << 32) | (uint32_t)lo);
 }
 
-__device__ __forceinline__ long long icp_term(int j, int4 q, int4 c)
+// Collects wave-wide sums, sum j in lane j.
+struct WaveSums {
+    int lane, lo, hi;
+    __device__ __forceinline__ explicit WaveSums(int l) : lane(l), lo(0), hi(0) {}
+    __device__ __forceinline__ void set(int j, long long x)
+    {
+        x = dpp_add64<0x111, 0xF>(x);      // row_shr 1, 2, 4, 8: lane 15 of each row holds the row's sum
+        x = dpp_add64<0x112, 0xF>(x);
+        x = dpp_add64<0x114, 0xF>(x);
+        x = dpp_add64<0x118, 0xF>(x);
+        x = dpp_add64<0x142, 0xA>(x);      // row_bcast 15 into rows 1 and 3, 31 into rows 2 and 3
+        x = dpp_add64<0x143, 0xC>(x);
+        const int tl = __builtin_amdgcn_readlane((int)(uint32_t)x, 63);
+        const int th = __builtin_amdgcn_readlane((int)(uint32_t)((unsigned long long)x >> 32), 63);
+        lo = lane == j ? tl : lo;
+        hi = lane == j ? th : hi;
+    }
+    __device__ __forceinline__ long long value() const
+    {
+        return (long long)(((unsigned long long)(uint32_t)hi << 32) | (uint32_t)lo);
+    }
+};
+
+// The ICP target in tiles of 4x4 pixels, 16 lanes each: the tile's points
+// side by side as (X, Y, Z, -), Z = kNoPoint where there is none that can
+// match (label volumes: off the label), and their box (1/16 mm), {lo, -} and
+// {hi, -}, lo > hi without a point.  With the label folded in here the search
+// needs no second, dependent load where a nearer point turns up.  Also zeroes
+// the cursor.
+__global__ __launch_bounds__(256) void icp_target_kernel(IcpArgs a)
 {
-    if (j == 0) return 1;
-    if (j < 4) return icp_pick(j - 1, q.x, q.y, q.z);
-    if (j < 7) return icp_pick(j - 4, c.x, c.y, c.z);
-    if (j < 16) return icp_pick((j - 7) / 3, q.x, q.y, q.z) * icp_pick((j - 7) % 3, q.x, q.y, q.z);
-    return icp_pick((j - 16) / 3, q.x, q.y, q.z) * icp_pick((j - 16) % 3, c.x, c.y, c.z);
+    const SceneDev &s = a.s;
+    if (blockIdx.x == 0 && threadIdx.x == 0) a.cursor[0] = 0;
+    const int tiles_x = (s.W + kIcpTile - 1) / kIcpTile, tiles_y = (s.H + kIcpTile - 1) / kIcpTile;
+    const int t = blockIdx.x * 16 + (threadIdx.x >> 4), lane = threadIdx.x & 15;
+    const int i = (t % tiles_x) * kIcpTile + (lane & 3), j = (t / tiles_x) * kIcpTile + (lane >> 2);
+    const bool label_mode = (s.flags & (3u << 4)) == (2u << 4);
+    int lo[3] = {1 << 30, 1 << 30, 1 << 30}, hi[3] = {-(1 << 30), -(1 << 30), -(1 << 30)};
+    int4 o = make_int4(0, 0, kNoPoint, 0);
+    if (i < s.W && j < s.H) {
+        const int pix = j * s.W + i;
+        o = gld(s.opt + pix);
+        if (o.z != kNoPoint && (!(label_mode && s.labels) || gld(s.labels + pix) == a.label)) {
+            lo[0] = hi[0] = o.x;
+            lo[1] = hi[1] = o.y;
+            lo[2] = hi[2] = o.z;
+        } else {
+            o.z = kNoPoint;
+        }
+    }
+    if (t < tiles_x * tiles_y) a.target[16 * (size_t)t + lane] = o;
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+        for (int off = 8; off > 0; off >>= 1) {
+            lo[c] = min(lo[c], __shfl_xor(lo[c], off));
+            hi[c] = max(hi[c], __shfl_xor(hi[c], off));
+        }
+    if (lane == 0 && t < tiles_x * tiles_y) {
+        a.boxes[2 * t] = make_int4(lo[0], lo[1], lo[2], 0);
+        a.boxes[2 * t + 1] = make_int4(hi[0], hi[1], hi[2], 0);
+    }
+}
+
+// Per tile, the box of the 4x4 tiles from it on (16x16 pixels, clipped to the
+// image), after the tiles' own: one test then rules out sixteen.
+__global__ __launch_bounds__(256) void icp_target_wide_kernel(IcpArgs a)
+{
+    const int tiles_x = (a.s.W + kIcpTile - 1) / kIcpTile, tiles_y = (a.s.H + kIcpTile - 1) / kIcpTile;
+    const int t = blockIdx.x * 256 + threadIdx.x, n = tiles_x * tiles_y;
+    if (t >= n) return;
+    const int ty = t / tiles_x, tx = t - ty * tiles_x;
+    int4 lo = make_int4(1 << 30, 1 << 30, 1 << 30, 0), hi = make_int4(-(1 << 30), -(1 << 30), -(1 << 30), 0);
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+        // past the edge: the last tile again
+        const int u = min(ty + (k >> 2), tiles_y - 1) * tiles_x + min(tx + (k & 3), tiles_x - 1);
+        const int4 l = gld(a.boxes + 2 * u), h = gld(a.boxes + 2 * u + 1);
+        lo = make_int4(min(lo.x, l.x), min(lo.y, l.y), min(lo.z, l.z), 0);
+        hi = make_int4(max(hi.x, h.x), max(hi.y, h.y), max(hi.z, h.z), 0);
+    }
+    a.boxes[2 * (n + t)] = lo;
+    a.boxes[2 * (n + t) + 1] = hi;
+}
+
+// v of lane K of the quad, for the whole quad.
+template <int K>
+__device__ __forceinline__ int quad_lane(int v)
+{
+    return __builtin_amdgcn_update_dpp(v, v, K * 0x55, 0xF, 0xF, false);    // quad_perm [K, K, K, K]
+}
+// Least value over the four lanes of a quad.
+__device__ __forceinline__ int quad_min(int v)
+{
+    v = min(v, __builtin_amdgcn_update_dpp(v, v, 0xB1, 0xF, 0xF, false));    // quad_perm [1, 0, 3, 2]
+    return min(v, __builtin_amdgcn_update_dpp(v, v, 0x4E, 0xF, 0xF, false)); // quad_perm [2, 3, 0, 1]
+}
+
+// 1 / x for whole x >= 1, within a few ulps (v_rcp_f64 and one Newton step).
+__device__ __forceinline__ double icp_rcp(double x)
+{
+    const double y = __builtin_amdgcn_rcp(x);
+    return y * (2.0 - x * y);
+}
+
+// Pixels [w[0], w[2]] x [w[1], w[3]], inside `box`, that hold every observed
+// point within r of q (1/16 mm); false when there are none.  An observed
+// point at depth d (mm) with |Xq - qx| <= r has rint(kx[i] d) in
+// [qx - r, qx + r], so kx[i] d lies within half a unit of that range, for d
+// in [(qz - r) / 16, (qz + r) / 16]; one pixel of margin on each side, far
+// above the rounding.  The quad's lane `sub` computes w[sub], the upper
+// bounds as the negated lower bounds of the mirrored axis.
+__device__ __forceinline__ bool icp_window(const SceneDev &s, int4 q, int r, const int *box, int sub, int w[4])
+{
+    const int dlo = q.z - r <= 16 ? 1 : (q.z - r + 15) >> 4;
+    const int dhi = min(65534, (q.z + r) >> 4);
+    if (q.z + r < 16 || dlo > dhi) return false;
+    const double ilo = icp_rcp((double)dlo), ihi = icp_rcp((double)dhi);
+    const bool row = sub & 1, up = sub & 2;
+    const double f16 = (double)(row ? s.fy : s.fx) / 16.0, c = (double)(row ? s.cy : s.cx);
+    const int qv = row ? q.y : q.x;
+    const double e = (double)((up ? -qv : qv) - r) - 0.5;
+    const double v = (up ? -c : c) + f16 * fmin(e * ilo, e * ihi);
+    const int g = (int)floor(fmax(fmin(v, 1e8), -1e8)) - 1;
+    const int bound = up ? min(-g, row ? box[3] : box[2]) : max(g, row ? box[1] : box[0]);
+    w[0] = quad_lane<0>(bound);
+    w[1] = quad_lane<1>(bound);
+    w[2] = quad_lane<2>(bound);
+    w[3] = quad_lane<3>(bound);
+    return w[0] <= w[2] && w[1] <= w[3];
+}
+
+// Squared length of an offset in 1/16 mm, capped: the components saturate to
+// 16 bits (v_cvt_pk_i16_i32) and two v_dot2_i32_i16 sum their squares, at
+// most 3 * 2^30 < 2^32, so the value is exact below `cap` (< 2^30) and `cap`
+// at or above it.
+__device__ __forceinline__ int capped_d2(int dx, int dy, int dz, uint32_t cap)
+{
+    typedef short s2 __attribute__((ext_vector_type(2)));
+    const s2 xy = __builtin_amdgcn_cvt_pk_i16(dx, dy), z0 = __builtin_amdgcn_cvt_pk_i16(dz, 0);
+    const uint32_t d2 = (uint32_t)__builtin_amdgcn_sdot2(xy, xy, __builtin_amdgcn_sdot2(z0, z0, 0, false), false);
+    return (int)min(d2, cap);
+}
+
+// Box of target points.
+struct IcpBox {
+    int3 lo, hi;
+};
+__device__ __forceinline__ IcpBox icp_box(const int4 *boxes, int t)
+{
+    return IcpBox{opt_at(boxes, (uint32_t)(2 * t)), opt_at(boxes, (uint32_t)(2 * t + 1))};
 }
 
 // Nearest observed point of q (1/16 mm) within rq, ties to the lower pixel
-// index, or -1; with `labels`, only pixels carrying `label` count (label
-// volumes: the object's segment is the target), and `box` (inside the
-// image) holds every pixel that can count.  The whole wave searches, lanes
-// over a pixel window that holds every candidate: an observed point at
-// depth d (mm) with
-// |Xq - qx| <= rq has rint(kx[i] d) in [qx - rq, qx + rq], so
-// kx[i] d lies within half a unit of that range, for d in
-// [(qz - rq) / 16, (qz + rq) / 16]; one pixel of margin on each side.
-__device__ int icp_nn(const SceneDev &s, int4 q, int rq, int rq2, const int32_t *labels, int label, const int *box,
-                      int lane)
+// index, or -1; in label mode only pixels carrying the label count.  Four
+// lanes (a quad, `sub` 0..3) per point, every value but the lane's own tiles
+// alike in all four.  A first guess (`seed`, the match of the previous
+// update, else the pixel q projects to) bounds the distance, and with it the
+// window of pixels that can hold a nearer point: a surface point's nearest
+// neighbour lies a few mm away where rq is 20 mm.  The window's 4x4 tiles go
+// by their boxes of target points, the nearest first and only while one comes
+// as near as the best; sixteen tiles through one wider box before, so that a
+// point with no match within rq costs a few box tests.
+//
+// What bounds it is VALU issue, the search's own integer work; with one lane
+// per point it was the rate of distinct cache lines (every load of a scan
+// touched 64), where a quad reads 64 contiguous bytes per load.
+__device__ __forceinline__ int icp_nn(const IcpArgs &a, int4 q, int seed, int sub)
 {
-    const int dlo = q.z - rq <= 16 ? 1 : (q.z - rq + 15) / 16;
-    const int dhi = min(65534, (q.z + rq) / 16);
-    if (q.z + rq < 16 || dlo > dhi) return -1;
-    const double lo_d = (double)dlo, hi_d = (double)dhi;
-    int b[4];
-    const int qv[2] = {q.x, q.y};
-    for (int ax = 0; ax < 2; ++ax) {
-        const double f16 = (double)(ax == 0 ? s.fx : s.fy) / 16.0, c = (double)(ax == 0 ? s.cx : s.cy);
-        const double lo = (double)(qv[ax] - rq) - 0.5, hi = (double)(qv[ax] + rq) + 0.5;
-        const double a = c + f16 * fmin(lo / lo_d, lo / hi_d), z = c + f16 * fmax(hi / lo_d, hi / hi_d);
-        b[2 * ax] = (int)floor(fmax(fmin(a, 1e8), -1e8)) - 1;
-        b[2 * ax + 1] = (int)ceil(fmax(fmin(z, 1e8), -1e8)) + 1;
+    const SceneDev &s = a.s;
+    if (q.z + a.rq < 16 || a.box[0] > a.box[2] || a.box[1] > a.box[3]) return -1;
+    const uint32_t cap = (uint32_t)a.rq2 + 1;
+    // the best so far: squared distance and pixel; nothing yet: above rq^2
+    int bd2 = a.rq2 + 1, bpix = -1;
+    auto d2_of = [&](int3 o) { return capped_d2(o.x - q.x, o.y - q.y, o.z - q.z, cap); };
+    const int tiles_x = (s.W + kIcpTile - 1) / kIcpTile;
+    if (seed >= 0) {
+        bd2 = d2_of(opt_at(s.opt, (uint32_t)seed));
+        bpix = seed;
+    } else if (q.z > 0) {
+        const float iz = 1.0f / (float)q.z;
+        const float u = s.cx + s.fx * (float)q.x * iz, v = s.cy + s.fy * (float)q.y * iz;
+        const int i = (int)fmaxf(fminf(rintf(u), (float)a.box[2]), (float)a.box[0]);
+        const int j = (int)fmaxf(fminf(rintf(v), (float)a.box[3]), (float)a.box[1]);
+        const int t = (j / kIcpTile) * tiles_x + i / kIcpTile;
+        bd2 = d2_of(opt_at(a.target, (uint32_t)(16 * t + kIcpTile * (j % kIcpTile) + i % kIcpTile)));
+        bpix = j * s.W + i;
     }
-    const int i0 = max(b[0], box[0]), i1 = min(b[1], box[2]), j0 = max(b[2], box[1]), j1 = min(b[3], box[3]);
-    if (i0 > i1 || j0 > j1) return -1;
-    const int ww = i1 - i0 + 1, n = ww * (j1 - j0 + 1);
-    const float inv = 1.0f / (float)ww;
-    const int lim = rq + 1;
-    unsigned long long best = ~0ULL;
-    for (int k0 = 0; k0 < n; k0 += 64) {
-        const int k = k0 + lane;
-        if (k < n) {
-            const int r = window_row(k, ww, inv);
-            const int pix = (j0 + r) * s.W + i0 + (k - r * ww);
-            const int4 o = gld(s.opt + pix);
-            const int dx = clamp_i32(o.x - q.x, -lim, lim);
-            const int dy = clamp_i32(o.y - q.y, -lim, lim);
-            const int dz = clamp_i32(o.z - q.z, -lim, lim);
-            const int d2 = __mul24(dx, dx) + __mul24(dy, dy) + __mul24(dz, dz);
-            if (d2 <= rq2 && (!labels || gld(labels + pix) == label)) {
-                const unsigned long long key = ((unsigned long long)(uint32_t)d2 << 32) | (uint32_t)pix;
-                best = key < best ? key : best;
+    // every point at least as near as the best lies within r: r^2 >= its d2
+    int r = a.rq;
+    if (bd2 <= a.rq2) r = min(a.rq, (int)sqrtf((float)bd2) + 1);
+    int w[4];
+    if (icp_window(s, q, r, a.box, sub, w)) {
+        const int tx0 = w[0] / kIcpTile, ty0 = w[1] / kIcpTile, tx1 = w[2] / kIcpTile, ty1 = w[3] / kIcpTile;
+        const int n_tiles = tiles_x * ((s.H + kIcpTile - 1) / kIcpTile);
+        // blocks of 4x4 wide boxes, each of 4x4 tiles: the quad's lane `sub`
+        // holds column `sub` of either, as keys (box distance << 4 | index)
+        constexpr int kNone = 0x7FFFFFFF;
+        for (int by = ty0; by <= ty1; by += 16)
+            for (int bx = tx0; bx <= tx1; bx += 16) {
+                int wide[4], tile[4];
+                auto test = [&](int first, int x, int y0, int step, int key[4]) {
+                    IcpBox box[4];
+#pragma unroll
+                    for (int k = 0; k < 4; ++k)
+                        box[k] = icp_box(a.boxes, first + min(y0 + step * k, ty1) * tiles_x + min(x, tx1));
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        const IcpBox &b = box[k];
+                        const int d2 = capped_d2(max(max(b.lo.x - q.x, q.x - b.hi.x), 0),
+                                                 max(max(b.lo.y - q.y, q.y - b.hi.y), 0),
+                                                 max(max(b.lo.z - q.z, q.z - b.hi.z), 0), cap);
+                        key[k] = x <= tx1 && y0 + step * k <= ty1 ? (d2 << 4) | (4 * k + sub) : kNone;
+                    }
+                };
+                // the quad's nearest key of those left, taken out; false when
+                // none comes as near as the best (of points within rq: a box
+                // or point at the cap is out of reach)
+                auto next = [&](int key[4], int &got) {
+                    got = quad_min(min(min(key[0], key[1]), min(key[2], key[3])));
+#pragma unroll
+                    for (int k = 0; k < 4; ++k)
+                        if (key[k] == got) key[k] = kNone;
+                    return (got >> 4) <= min(bd2, a.rq2);
+                };
+                int c, f;
+                test(n_tiles, bx + 4 * sub, by, 4, wide);
+                while (next(wide, c)) {
+                    const int cx = bx + 4 * (c & 3), cy = by + (c & 12);
+                    test(0, cx + sub, cy, 1, tile);
+                    while (next(tile, f)) {
+                        const int tx = cx + (f & 3), ty = cy + ((f >> 2) & 3);
+                        int3 o[4];
+#pragma unroll
+                        for (int k = 0; k < 4; ++k)
+                            o[k] = opt_at(a.target, (uint32_t)(16 * (ty * tiles_x + tx) + 4 * k + sub));
+                        // lane `sub` reads column `sub`: the key's low bits count the tile's pixels row by row
+                        int m = kNone;
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) m = min(m, (d2_of(o[k]) << 4) | (4 * k + sub));
+                        m = quad_min(m);
+                        const int pix = (kIcpTile * ty + ((m >> 2) & 3)) * s.W + kIcpTile * tx + (m & 3);
+                        if ((m >> 4) < bd2 || ((m >> 4) == bd2 && pix < bpix)) {
+                            bd2 = m >> 4;
+                            bpix = pix;
+                        }
+                    }
+                }
             }
-        }
     }
-    for (int off = 32; off > 0; off >>= 1) {
-        const unsigned long long o = __shfl_xor(best, off);
-        best = o < best ? o : best;
-    }
-    return best == ~0ULL ? -1 : (int)(best & 0xFFFFFFFFu);
+    return bd2 <= a.rq2 ? bpix : -1;
 }
 
 // One ICP update from the sums (n, q, c, q q^T, q c^T): the increment about
@@ -94,7 +288,7 @@ __device__ int icp_nn(const SceneDev &s, int4 q, int rq, int rq2, const int32_t 
 // unit quaternion (1, w'/2) and the centroid moved onto mc.  Every step
 // uses + - * / and sqrt only, left to right.  Returns 1 when the 6-DoF
 // system is singular (nothing changes).
-__device__ int icp_update(const long long *z, int dof, const double u[3], double *A, double *b)
+__device__ __noinline__ int icp_update(const long long *z, int dof, const double u[3], double *A, double *b)
 {
     const double n = (double)z[0];
     double mq[3], mc[3], S[3][3], H[3][3];
@@ -216,13 +410,14 @@ __device__ __forceinline__ void unit_of(const int c[3], double n[3])
     n[2] = z / l;
 }
 
-// Term j (of kGicpSums) of one match q -> c: with the plane covariances
+// The kGicpSums terms of one match q -> c per lane, summed over the wave
+// (lanes without a match, `has` false, add nothing): with the plane covariances
 // I - (1 - 1/1024) n n^T of the source normal turned by A and of the target
 // normal (I without one), M = (C_a + C_b)^-1 by the adjugate, K = -[q - mu]x
 // and e = c - q, the Gauss-Newton matrix [[K^T M K, K^T M], [M K, M]] (upper
 // entries row by row) and right-hand side [K^T M e; M e], times 1024, rounded.
-__device__ long long gicp_term(int j, int4 q, int4 c, const long long mu[3], int has_a, const double na[3],
-                               int has_b, const double nb[3], const double *A)
+__device__ __forceinline__ void gicp_terms(bool has, int4 q, int3 c, const long long mu[3], int has_a, const double na[3],
+                                           int has_b, const double nb[3], const double *A, WaveSums &w)
 {
     const double eps = 1.0 / 1024.0;
     double ra[3] = {0.0, 0.0, 0.0};
@@ -259,31 +454,28 @@ __device__ long long gicp_term(int j, int4 q, int4 c, const long long mu[3], int
         for (int k = 0; k < 3; ++k) MK[r][k] = (M[r][0] * Kq[0][k] + M[r][1] * Kq[1][k]) + M[r][2] * Kq[2][k];
         Me[r] = (M[r][0] * e[0] + M[r][1] * e[1]) + M[r][2] * e[2];
     }
-    double v;
-    if (j < 21) {
-        // (r, k) of upper entry j, row by row
-        int r = 0, k = j;
-        while (k >= 6 - r) {
-            k -= 6 - r;
-            ++r;
+    int j = 0;
+#pragma unroll
+    for (int r = 0; r < 6; ++r)
+#pragma unroll
+        for (int k = r; k < 6; ++k) {
+            double v;
+            if (r < 3 && k < 3) v = (Kq[0][r] * MK[0][k] + Kq[1][r] * MK[1][k]) + Kq[2][r] * MK[2][k];
+            else if (r < 3) v = MK[k - 3][r];
+            else v = M[r - 3][k - 3];
+            w.set(j++, has ? (long long)rint(v * 1024.0) : 0);
         }
-        k += r;
-        if (r < 3 && k < 3) v = (Kq[0][r] * MK[0][k] + Kq[1][r] * MK[1][k]) + Kq[2][r] * MK[2][k];
-        else if (r < 3) v = MK[k - 3][r];
-        else v = M[r - 3][k - 3];
-    } else if (j < 24) {
-        const int r = j - 21;
-        v = (Kq[0][r] * Me[0] + Kq[1][r] * Me[1]) + Kq[2][r] * Me[2];
-    } else {
-        v = Me[j - 24];
-    }
-    return (long long)rint(v * 1024.0);
+#pragma unroll
+    for (int r = 0; r < 3; ++r)
+        w.set(j++, has ? (long long)rint(((Kq[0][r] * Me[0] + Kq[1][r] * Me[1]) + Kq[2][r] * Me[2]) * 1024.0) : 0);
+#pragma unroll
+    for (int r = 0; r < 3; ++r) w.set(j++, has ? (long long)rint(Me[r] * 1024.0) : 0);
 }
 
 // The GICP update from the fixed-point sums: H w = g by Cholesky (a pivot
 // <= 0 returns 1, nothing changes), the rotation the unit quaternion
 // (1, w/2) normalised, and (A, b) <- (Rc A, Rc (b - mu) + mu + t).
-__device__ int gicp_update(const long long *z, const long long mu[3], double *A, double *b)
+__device__ __noinline__ int gicp_update(const long long *z, const long long mu[3], double *A, double *b)
 {
     double Hm[6][6], g[6];
     int t = 0;
@@ -343,20 +535,20 @@ __device__ int gicp_update(const long long *z, const long long mu[3], double *A,
     return 0;
 }
 
-__global__ void icp_zero_kernel(int *cursor)
-{
-    if (threadIdx.x == 0) cursor[threadIdx.x] = 0;
-}
-
 // ICP refinement (Sec. IV-A "Parallel M2M GICP"; point-to-point): one pose
 // per work-group at a time, taken through a cursor.  The pose is rendered
 // into the work-group's device tile, its rendered points (R minus C on the
 // ICP stride grid) collected, then each iteration maps them by the current
 // transform (rounded to 1/16 mm), stops when no mapped point moved, matches
-// each to its nearest observed point within rho (one wave per point), sums
+// each to its nearest observed point within rho (four lanes per point), sums
 // the pairs exactly in int64 and updates the transform on one thread.
-template <int BLOCK>
-__global__ __launch_bounds__(BLOCK) void icp_kernel(IcpArgs a)
+// Measured (640x480, rho 20 mm, ten updates, about 900 source points): 1,600
+// 3-DoF poses against a label 25.2 -> 2.6 ms, 128 GICP poses of a 20k-triangle
+// mesh 12.6 -> 0.9 ms; before, a wave scanned the whole window of each point
+// and computed each GICP term set once per match.  Of a pose's time now: the
+// search 70 %, the sums 18 %, the raster 5 %.
+template <int BLOCK, bool GICP>
+__global__ __launch_bounds__(BLOCK, 4) void icp_kernel(IcpArgs a)
 {
     constexpr int NW = BLOCK / 64;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -364,14 +556,14 @@ __global__ __launch_bounds__(BLOCK) void icp_kernel(IcpArgs a)
     const MeshDev &m = a.m;
     extern __shared__ uint32_t icp_lds[];
     __shared__ int s_pose, s_n, s_box[4], s_changed, s_stop;
-    __shared__ long long s_red[NW][kRedSums];
-    __shared__ double s_A[9], s_b[3];
+    __shared__ long long s_red[NW][kRedSums], s_tot[kRedSums];
+    __shared__ double s_A[9], s_b[3], s_u[3];
     __shared__ long long s_mu[3];
     uint32_t *tile = a.tiles + (size_t)blockIdx.x * s.W * s.H;
     int4 *src = a.pts + (size_t)blockIdx.x * (gicp_slots(a.method)) * a.pts_cap;
     int4 *qb = src + a.pts_cap;
     int4 *nrm = qb + a.pts_cap;            // GICP: integer source normals (x, y, z, has)
-    const bool gicp = a.method == 1;
+    constexpr bool gicp = GICP;
     const int gap = a.rq >> 4;
     const bool mark = (s.flags & 2u) != 0;
     const bool label_mode = (s.flags & (3u << 4)) == (2u << 4);
@@ -419,6 +611,9 @@ __global__ __launch_bounds__(BLOCK) void icp_kernel(IcpArgs a)
             s_box[2] = w;
             s_box[3] = h;
             s_n = 0;
+            const double v[3] = {(double)P[2], (double)P[6], (double)P[10]};
+            const double nv = sqrt((v[0] * v[0] + v[1] * v[1]) + v[2] * v[2]);
+            for (int c = 0; c < 3; ++c) s_u[c] = v[c] / nv;
             for (int k = 0; k < 9; ++k) s_A[k] = (k % 4 == 0) ? 1.0 : 0.0;
             s_b[0] = s_b[1] = s_b[2] = 0.0;
         }
@@ -477,13 +672,7 @@ __global__ __launch_bounds__(BLOCK) void icp_kernel(IcpArgs a)
         }
         __syncthreads();
         const int ns = __builtin_amdgcn_readfirstlane(s_n);
-        double u[3] = {0.0, 0.0, 0.0};
         int iters = 0, matched = 0;
-        if (tid == 0) {
-            const double v[3] = {(double)P[2], (double)P[6], (double)P[10]};
-            const double nrm = sqrt((v[0] * v[0] + v[1] * v[1]) + v[2] * v[2]);
-            for (int c = 0; c < 3; ++c) u[c] = v[c] / nrm;
-        }
         for (int it = 0; it < a.iterations; ++it) {
             if (tid == 0) s_changed = 0;
             __syncthreads();
@@ -497,44 +686,69 @@ __global__ __launch_bounds__(BLOCK) void icp_kernel(IcpArgs a)
                                            + s_A[3 * c + 2] * (double)sp.z) + s_b[c]);
                     qv[c] = (int)fmax(fmin(v, 268435456.0), -268435456.0);
                 }
-                const int4 q = make_int4(qv[0], qv[1], qv[2], 0);
+                int4 q = make_int4(qv[0], qv[1], qv[2], -1);
                 if (it == 0) {
                     ch = true;
                 } else {
                     const int4 o = qb[t];
                     ch |= o.x != q.x || o.y != q.y || o.z != q.z;
+                    q.w = o.w;
                 }
                 qb[t] = q;
             }
             if (ch) s_changed = 1;
             __syncthreads();
             if (!__builtin_amdgcn_readfirstlane(s_changed)) break;
-            long long acc = 0;
-            for (int t = wave; t < ns; t += NW) {
+            for (int t = tid >> 2; t < ns; t += BLOCK / 4) {
                 const int4 q = qb[t];
-                const int nn = icp_nn(s, q, a.rq, a.rq2, label_mode ? s.labels : nullptr, a.label, a.box, lane);
-                if (gicp && lane == 0) qb[t].w = nn;     // the match, for the second pass
-                if (nn >= 0) {
-                    const int4 c = gld(s.opt + nn);
-                    if (lane < kIcpSums) acc += icp_term(lane, q, c);
+                // the match: also the next iteration's first guess, and read by GICP's second pass
+                const int nn = icp_nn(a, q, q.w, lane & 3);
+                if ((lane & 3) == 0) qb[t].w = nn;
+            }
+            __syncthreads();
+            // the pairs' sums, 64 points at a time: sum j in lane j
+            long long acc = 0;
+            for (int t0 = wave * 64; t0 < ns; t0 += BLOCK) {
+                const int t = t0 + lane;
+                int4 q = make_int4(0, 0, 0, -1);
+                if (t < ns) q = qb[t];
+                const bool has = q.w >= 0;
+                const int qv[3] = {has ? q.x : 0, has ? q.y : 0, has ? q.z : 0};
+                WaveSums w(lane);
+                w.set(0, has);
+#pragma unroll
+                for (int k = 0; k < 3; ++k) w.set(1 + k, qv[k]);
+                if (!gicp) {     // GICP takes the matches' centre only
+                    const int3 c = opt_at(s.opt, (uint32_t)max(q.w, 0));
+                    const int cv[3] = {has ? c.x : 0, has ? c.y : 0, has ? c.z : 0};
+#pragma unroll
+                    for (int k = 0; k < 3; ++k) w.set(4 + k, cv[k]);
+#pragma unroll
+                    for (int k = 0; k < 9; ++k) {
+                        if (k / 3 <= k % 3) w.set(7 + k, (long long)qv[k / 3] * (long long)qv[k % 3]);
+                        w.set(16 + k, (long long)qv[k / 3] * (long long)cv[k % 3]);
+                    }
                 }
+                acc += w.value();
             }
             if (lane < kIcpSums) s_red[wave][lane] = acc;
             __syncthreads();
             if (tid < kIcpSums) {
+                // q q^T is symmetric: its lower entries come from the upper ones
+                const int up = tid == 10 ? 8 : (tid == 13 ? 9 : (tid == 14 ? 12 : tid));
                 long long z = 0;
-                for (int v = 0; v < NW; ++v) z += s_red[v][tid];
-                s_red[0][tid] = z;
+                for (int v = 0; v < NW; ++v) z += s_red[v][up];
+                s_tot[tid] = z;
             }
             __syncthreads();
             if (tid == 0) {
                 int stop = 0;
-                matched = (int)s_red[0][0];
-                if (s_red[0][0] < a.min_points) stop = 1;
+                matched = (int)s_tot[0];
+                if (s_tot[0] < a.min_points) stop = 1;
                 else if (gicp) {
                     // the centre of the matched points, rounded: exact integer sums
-                    for (int c = 0; c < 3; ++c) s_mu[c] = (long long)rint((double)s_red[0][1 + c] / (double)s_red[0][0]);
-                } else if (icp_update(s_red[0], a.dof, u, s_A, s_b)) {
+                    for (int c = 0; c < 3; ++c) s_mu[c] = (long long)rint((double)s_tot[1 + c] / (double)s_tot[0]);
+                } else if (icp_update(s_tot, a.dof, s_u, s_A, s_b)) {
                     stop = 1;
                 } else {
                     iters = it + 1;
@@ -545,34 +759,41 @@ __global__ __launch_bounds__(BLOCK) void icp_kernel(IcpArgs a)
             if (__builtin_amdgcn_readfirstlane(s_stop)) break;
             if (gicp) {
                 // second pass: the Gauss-Newton terms of every match, one
-                // wave per match, lane j summing term j
+                // match per lane
                 const long long mu[3] = {s_mu[0], s_mu[1], s_mu[2]};
-                long long gacc = 0;
-                for (int t = wave; t < ns; t += NW) {
-                    const int4 q = qb[t];
-                    if (q.w < 0) continue;
-                    const int4 c = gld(s.opt + q.w);
-                    const int4 cs = nrm[t];
+                acc = 0;
+                for (int t0 = wave * 64; t0 < ns; t0 += BLOCK) {
+                    const int t = t0 + lane;
+                    int4 q = make_int4(0, 0, 0, -1), cs = make_int4(0, 0, 0, 0);
+                    if (t < ns) {
+                        q = qb[t];
+                        cs = nrm[t];
+                    }
+                    const bool has = q.w >= 0;
+                    const int nn = max(q.w, 0);
+                    const int3 c = opt_at(s.opt, (uint32_t)nn);
                     double na[3] = {0.0, 0.0, 0.0}, nb[3] = {0.0, 0.0, 0.0};
                     const int csv[3] = {cs.x, cs.y, cs.z};
                     if (cs.w) unit_of(csv, na);
-                    const int pi = q.w % s.W, pj = q.w / s.W;
+                    const int pj = nn / s.W, pi = nn - pj * s.W;
                     auto odepth = [&](int ii, int jj) -> int { return gld(s.depth + jj * s.W + ii); };
                     int cb[3];
                     const int has_b = pixel_normal(s, pi, pj, gap, odepth, cb);
                     if (has_b) unit_of(cb, nb);
-                    if (lane < kGicpSums) gacc += gicp_term(lane, q, c, mu, cs.w, na, has_b, nb, s_A);
+                    WaveSums w(lane);
+                    gicp_terms(has, q, c, mu, cs.w, na, has_b, nb, s_A, w);
+                    acc += w.value();
                 }
-                if (lane < kGicpSums) s_red[wave][lane] = gacc;
+                if (lane < kGicpSums) s_red[wave][lane] = acc;
                 __syncthreads();
                 if (tid < kGicpSums) {
                     long long z = 0;
                     for (int v = 0; v < NW; ++v) z += s_red[v][tid];
-                    s_red[0][tid] = z;
+                    s_tot[tid] = z;
                 }
                 __syncthreads();
                 if (tid == 0) {
-                    const int stop = gicp_update(s_red[0], mu, s_A, s_b);
+                    const int stop = gicp_update(s_tot, mu, s_A, s_b);
                     if (!stop) iters = it + 1;
                     s_stop = stop;
                 }
@@ -582,6 +803,7 @@ __global__ __launch_bounds__(BLOCK) void icp_kernel(IcpArgs a)
         }
         if (tid == 0) {
             float *out = a.refined + 12 * (size_t)p;
+            const float *P = a.poses + 12 * (size_t)p;     // read again: not held through the iterations
             for (int r = 0; r < 3; ++r) {
                 for (int c = 0; c < 3; ++c)
                     out[4 * r + c] = (float)((s_A[3 * r] * (double)P[c] + s_A[3 * r + 1] * (double)P[4 + c])
@@ -652,23 +874,40 @@ hipError_t launch_proposals(const ProposalArgs &a, hipStream_t st)
     return hipGetLastError();
 }
 
-hipError_t launch_icp(const IcpArgs &a, int grid, hipStream_t st)
+hipError_t launch_icp(const IcpArgs &a, int block, int grid, hipStream_t st)
 {
-    icp_zero_kernel<<<1, 1, 0, st>>>(a.cursor);
-    icp_kernel<1024><<<grid, 1024, (size_t)a.lds_words * 4, st>>>(a);
+    const int tiles = (int)icp_tiles(a.s.W, a.s.H);
+    icp_target_kernel<<<(tiles + 15) / 16, 256, 0, st>>>(a);
+    icp_target_wide_kernel<<<(tiles + 255) / 256, 256, 0, st>>>(a);
+    const size_t lds = (size_t)a.lds_words * 4;
+    if (block == 512) {
+        if (a.method == 1) icp_kernel<512, true><<<grid, 512, lds, st>>>(a);
+        else icp_kernel<512, false><<<grid, 512, lds, st>>>(a);
+    } else {
+        if (a.method == 1) icp_kernel<1024, true><<<grid, 1024, lds, st>>>(a);
+        else icp_kernel<1024, false><<<grid, 1024, lds, st>>>(a);
+    }
     return hipGetLastError();
 }
 
-hipError_t prepare_icp_kernel(int lds_per_group, int *lds_words)
+hipError_t prepare_icp_kernel(int lds_per_group, int lds_words[2])
 {
-    const void *f = (const void *)icp_kernel<1024>;
-    hipFuncAttributes at{};
-    hipError_t e = hipFuncGetAttributes(&at, f);
-    if (e != hipSuccess) return e;
-    const int dyn = lds_per_group - (int)at.sharedSizeBytes;
-    e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, dyn);
-    *lds_words = e == hipSuccess ? dyn / 4 : 0;
-    return e;
+    lds_words[0] = lds_words[1] = 0;
+    const void *ks[2][2] = {{(const void *)icp_kernel<512, false>, (const void *)icp_kernel<512, true>},
+                            {(const void *)icp_kernel<1024, false>, (const void *)icp_kernel<1024, true>}};
+    for (int b = 0; b < 2; ++b) {
+        const int share = b == 0 ? lds_per_group / 2 : lds_per_group;
+        int st = 0;
+        for (const void *f : ks[b]) {
+            hipFuncAttributes at{};
+            if (hipError_t e = hipFuncGetAttributes(&at, f)) return e;
+            st = max(st, (int)at.sharedSizeBytes);
+        }
+        for (const void *f : ks[b])
+            if (hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, share - st)) return e;
+        lds_words[b] = (share - st) / 4;
+    }
+    return hipSuccess;
 }
 
 }  // namespace perch

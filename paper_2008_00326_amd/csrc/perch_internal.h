@@ -166,12 +166,22 @@ struct IcpArgs {
     int4 *pts;               // per work-group: pts_cap source points, pts_cap mapped points (w: the match),
                              // and for GICP pts_cap source normals
     size_t pts_cap;
+    int4 *target;            // the points that can match, 16 per 4x4 pixel tile, tiles row-major: (X, Y, Z, -)
+    int4 *boxes;             // per 4x4 pixel tile of the image, row-major, {lo, -}, {hi, -} of its target points;
+                             // then the same of the 4x4 tiles from each one on
     int *cursor;             // pose cursor, zeroed by the launch
 };
-hipError_t launch_icp(const IcpArgs &a, int grid, hipStream_t st);
-// Allow the ICP kernel all the LDS a work-group can hold beside its static
-// LDS (once per device); *lds_words receives that dynamic capacity.
-hipError_t prepare_icp_kernel(int lds_per_group, int *lds_words);
+constexpr int kIcpTile = 4;
+// Tiles of a W x H image (IcpArgs::target: 16 int4 each, boxes: four).
+inline size_t icp_tiles(int W, int H)
+{
+    return (size_t)((W + kIcpTile - 1) / kIcpTile) * ((H + kIcpTile - 1) / kIcpTile);
+}
+hipError_t launch_icp(const IcpArgs &a, int block, int grid, hipStream_t st);   // block 512 or 1024 threads
+// Allow the ICP kernels their share of the CU's LDS beside their static LDS
+// (once per device): half of it for 512 threads, all of it for 1024;
+// lds_words receives the dynamic capacity of each.
+hipError_t prepare_icp_kernel(int lds_per_group, int lds_words[2]);
 
 // 6-DoF pose proposals of one object: viewpoint x in-plane angle x depth.
 struct ProposalArgs {

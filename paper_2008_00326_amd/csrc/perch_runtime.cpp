@@ -177,7 +177,7 @@ struct perch_ctx {
     perch_tuning tune{};                  // zeros: defaults
     int static_lds[3] = {0, 0, 0};        // static LDS bytes of the 256-, 512- and 1024-thread scoring kernels
     std::vector<Staging *> scene_stage;   // free pinned staging areas of scene uploads
-    int icp_lds_words = 0;                // dynamic LDS words of the ICP kernel
+    int icp_lds_words[2] = {0, 0};        // dynamic LDS words of the 512- and 1024-thread ICP kernels
     int msg_lds_words = 0;                // dynamic LDS words of the tree's successor kernel
     void *noalloc = nullptr;              // this device's address of the allocation-free path's scratch
 
@@ -745,7 +745,7 @@ perch_status perch_create(int device, size_t hbm_budget_bytes, perch_ctx **out)
     colour_table(lin);
     e = upload_colour_table(lin);
     if (e == hipSuccess) e = prepare_score_kernels((int)ctx->lds_max, ctx->static_lds);
-    if (e == hipSuccess) e = prepare_icp_kernel((int)ctx->lds_max, &ctx->icp_lds_words);
+    if (e == hipSuccess) e = prepare_icp_kernel((int)ctx->lds_max, ctx->icp_lds_words);
     if (e == hipSuccess) e = upload_msg_colour_table(lin);
     if (e == hipSuccess) e = upload_knn1_colour_table(lin);
     if (e == hipSuccess) e = prepare_msg_kernel((int)ctx->lds_max, &ctx->msg_lds_words);
@@ -1528,12 +1528,28 @@ perch_status perch_refine_poses(perch_ctx *ctx, int32_t scene_id, int32_t mesh_i
     hipStream_t st = pick_stream(ctx, hip_stream);
     StreamBufs &b = ctx->work[st];
     const SceneDev &s = si->second.dev;
-    const int grid = std::min(n, std::max(ctx->n_cu, 1));
     const size_t px = (size_t)s.W * s.H;
-    const size_t tiles_off = 256, pts_off = tiles_off + (size_t)grid * px * 4;
+    const size_t pts = (size_t)((s.W + prm->stride - 1) / prm->stride) * ((s.H + prm->stride - 1) / prm->stride);
+    const size_t boxes_off = 256, target_off = boxes_off + icp_tiles(s.W, s.H) * 4 * sizeof(int4);
+    const size_t tiles_off = target_off + icp_tiles(s.W, s.H) * 16 * sizeof(int4);
     const int slots = prm->method == PERCH_ICP_PLANE ? 3 : 2;   // source, mapped (+ normals for GICP)
-    const size_t bytes = pts_off + (size_t)grid * slots * px * sizeof(int4);
-    if (perch_status e = ctx->ensure(b.icp, bytes)) return e;
+    auto pts_at = [&](int groups) { return (tiles_off + (size_t)groups * px * 4 + 255) & ~(size_t)255; };
+    // Two 512-thread work-groups per compute unit once there are poses for
+    // them, so that one works while the other waits at a barrier or for its
+    // update on one thread (1,600 poses: 2.63 ms against 2.86 with one of
+    // 1024); below that a pose takes a whole compute unit, as it does where
+    // the scratch of twice the work-groups does not fit.
+    const int cu = std::max(ctx->n_cu, 1);
+    int block = n > cu ? 512 : 1024;
+    int grid = std::min(n, block == 512 ? 2 * cu : cu);
+    perch_status fit = ctx->ensure(b.icp, pts_at(grid) + (size_t)grid * slots * pts * sizeof(int4));
+    if (fit == PERCH_ENOMEM && block == 512) {
+        block = 1024;
+        grid = cu;
+        fit = ctx->ensure(b.icp, pts_at(grid) + (size_t)grid * slots * pts * sizeof(int4));
+    }
+    if (fit) return fit;
+    const size_t pts_off = pts_at(grid);
     IcpArgs a{};
     a.s = s;
     a.m = mi->second.dev;
@@ -1558,16 +1574,18 @@ perch_status perch_refine_poses(perch_ctx *ctx, int32_t scene_id, int32_t mesh_i
         a.box[2] = lb[0] + lb[2] - 1;
         a.box[3] = lb[1] + lb[3] - 1;
     }
-    a.lds_words = ctx->icp_lds_words;
+    a.lds_words = ctx->icp_lds_words[block == 512 ? 0 : 1];
     a.refined = refined_dev;
     a.iters = iters_dev;
     a.matched = matched_dev;
     char *base = (char *)b.icp.ptr;
     a.cursor = (int *)base;
+    a.boxes = (int4 *)(base + boxes_off);
+    a.target = (int4 *)(base + target_off);
     a.tiles = (uint32_t *)(base + tiles_off);
     a.pts = (int4 *)(base + pts_off);
-    a.pts_cap = px;
-    HIP_TRY(ctx->timed(kProfIcp, st, [&] { return launch_icp(a, grid, st); }));
+    a.pts_cap = pts;
+    HIP_TRY(ctx->timed(kProfIcp, st, [&] { return launch_icp(a, block, grid, st); }));
     ctx->mark_use(si->second.uses, st);
     ctx->mark_use(mi->second.uses, st);
     return ok();

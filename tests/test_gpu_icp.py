@@ -128,6 +128,36 @@ def test_refine_then_rescore_cfg2(ctx):
         ctx.unload_mesh(mid)
 
 
+@pytest.mark.parametrize("n,size,rho,method", [(280, (203, 151), 90.0, "point"), (20, (203, 151), 90.0, "plane"),
+                                               (20, (33, 30), 40.0, "point"), (3, (5, 3), 60.0, "point")])
+def test_search_blocks_and_ragged_tiles(ctx, n, size, rho, method):
+    """Search windows over several blocks of target tiles (64x64 pixels),
+    images that are no multiple of a tile, and launches on either side of the
+    two work-group sizes (more poses than compute units, and fewer)."""
+    W, H = size
+    K = (W, H, 1.1 * W, 1.05 * W, W / 2 + 0.3, H / 2 - 0.4)
+    cube = box((-40, -40, -20), (40, 40, 20), n=3, rgb_seed=2)
+    gt = pose_matrix(rot_x(2.3), (4, -6, 260))
+    d, _, _ = oracle.render(cube, gt, K)
+    rng = np.random.default_rng(77)
+    d = np.where(d > 0, d + rng.integers(-3, 4, d.shape), 0).astype(np.uint16)
+    poses = np.stack([pose_matrix(rot_x(2.3 + rng.normal(0, 0.2)), np.array([4, -6, 260]) + rng.normal(0, 25, 3))
+                      for _ in range(n)]).astype(np.float32)
+    say(f"icp blocks: {n} poses, {W}x{H}, rho {rho}, {method}")
+    sid = ctx.set_scene(K, d, None, delta_mm=8.0, mark_occluders=False)
+    mid = ctx.load_mesh(cube.xyz, cube.tri)
+    kw = dict(rho_mm=rho, iterations=3, stride=3 if W > 100 else 1, min_points=4)
+    got = gpu_refine(ctx, sid, mid, poses, dof=6, method=method, **kw)
+    ctx.drop_scene(sid)
+    ctx.unload_mesh(mid)
+    fn = oracle.icp if method == "point" else oracle.gicp
+    if method == "point":
+        kw["dof"] = 6
+    exp = fn(cube, TScene(K, d), poses, delta_mm=8.0, flags=0, threads=THREADS, **kw)
+    check(got, exp, f"{n} poses {W}x{H}")
+    assert exp[2].sum() > 0
+
+
 def test_icp_edges(ctx):
     K = (96, 72, 110.0, 110.0, 48.0, 36.0)
     cube = box((-20, -20, 0), (20, 20, 40), n=2, rgb_seed=1)
