@@ -238,6 +238,42 @@ __device__ __forceinline__ void project_box(const float *P, const float lo[3], c
     }
 }
 
+// project_box by a wave: lane l takes corner l & 7 and the extremes are
+// combined across the lanes, the same in all of them (minima and maxima of
+// the same values: the order does not matter).
+__device__ __forceinline__ void project_box_wave(const float *P, const float lo[3], const float hi[3], double pad,
+                                                 const SceneDev &s, int lane, double *umin, double *umax,
+                                                 double *vmin, double *vmax, double *zmin, double *zmax)
+{
+    const double x = (lane & 1) ? (double)hi[0] + pad : (double)lo[0] - pad;
+    const double y = (lane & 2) ? (double)hi[1] + pad : (double)lo[1] - pad;
+    const double z = (lane & 4) ? (double)hi[2] + pad : (double)lo[2] - pad;
+    const double X = (((double)P[0] * x + (double)P[1] * y) + (double)P[2] * z) + (double)P[3];
+    const double Y = (((double)P[4] * x + (double)P[5] * y) + (double)P[6] * z) + (double)P[7];
+    const double Z = (((double)P[8] * x + (double)P[9] * y) + (double)P[10] * z) + (double)P[11];
+    double e[6] = {1e300, 1e300, fmin(1e300, Z), -1e300, -1e300, fmax(-1e300, Z)};
+    if (Z > 0.0) {
+        const double u = (double)s.fx * X / Z + (double)s.cx;
+        const double v = (double)s.fy * Y / Z + (double)s.cy;
+        e[0] = fmin(1e300, u);
+        e[1] = fmin(1e300, v);
+        e[3] = fmax(-1e300, u);
+        e[4] = fmax(-1e300, v);
+    }
+    for (int o = 1; o < 8; o <<= 1)
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            e[k] = fmin(e[k], __shfl_xor(e[k], o));
+            e[3 + k] = fmax(e[3 + k], __shfl_xor(e[3 + k], o));
+        }
+    *umin = e[0];
+    *vmin = e[1];
+    *zmin = e[2];
+    *umax = e[3];
+    *vmax = e[4];
+    *zmax = e[5];
+}
+
 __device__ __forceinline__ void clip_box(double umin, double umax, double vmin, double vmax, int W, int H, int *x0,
                                          int *y0, int *w, int *h)
 {
@@ -438,6 +474,39 @@ __device__ __forceinline__ int clamp_i32(int x, int lo, int hi)
     int r;
     asm("v_med3_i32 %0, %1, %2, %3" : "=v"(r) : "v"(x), "v"(lo), "v"(hi));
     return r;
+}
+
+// Squared length of an offset in 1/16 mm, capped: the components saturate to
+// 16 bits (v_cvt_pk_i16_i32) and two v_dot2_i32_i16 sum their squares, at
+// most 3 * 2^30 < 2^32, so the value is exact below `cap` (< 2^30) and `cap`
+// at or above it.
+__device__ __forceinline__ int capped_d2(int dx, int dy, int dz, uint32_t cap)
+{
+    typedef short s2 __attribute__((ext_vector_type(2)));
+    const s2 xy = __builtin_amdgcn_cvt_pk_i16(dx, dy), z0 = __builtin_amdgcn_cvt_pk_i16(dz, 0);
+    const uint32_t d2 = (uint32_t)__builtin_amdgcn_sdot2(xy, xy, __builtin_amdgcn_sdot2(z0, z0, 0, false), false);
+    return (int)min(d2, cap);
+}
+
+// ------------------------------------------------------------------ waves
+
+__device__ __forceinline__ int wave_popc(bool pred)
+{
+    return __popcll(__ballot(pred));
+}
+
+// Number of lanes below this one whose bit is set in mask m.
+__device__ __forceinline__ int lane_rank(unsigned long long m)
+{
+    return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
+
+// Make the LDS writes of a wave visible to all its lanes.
+__device__ __forceinline__ void wave_lds_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
 }
 
 // ------------------------------------------------------------------ voxel hash

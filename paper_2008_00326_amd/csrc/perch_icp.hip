@@ -159,18 +159,6 @@ __device__ __forceinline__ bool icp_window(const SceneDev &s, int4 q, int r, con
     return w[0] <= w[2] && w[1] <= w[3];
 }
 
-// Squared length of an offset in 1/16 mm, capped: the components saturate to
-// 16 bits (v_cvt_pk_i16_i32) and two v_dot2_i32_i16 sum their squares, at
-// most 3 * 2^30 < 2^32, so the value is exact below `cap` (< 2^30) and `cap`
-// at or above it.
-__device__ __forceinline__ int capped_d2(int dx, int dy, int dz, uint32_t cap)
-{
-    typedef short s2 __attribute__((ext_vector_type(2)));
-    const s2 xy = __builtin_amdgcn_cvt_pk_i16(dx, dy), z0 = __builtin_amdgcn_cvt_pk_i16(dz, 0);
-    const uint32_t d2 = (uint32_t)__builtin_amdgcn_sdot2(xy, xy, __builtin_amdgcn_sdot2(z0, z0, 0, false), false);
-    return (int)min(d2, cap);
-}
-
 // Box of target points.
 struct IcpBox {
     int3 lo, hi;

@@ -224,34 +224,45 @@ inline MsgState msg_state_at(void *base, size_t n, bool rgb)
     st.near = (unsigned long long *)p;
     return st;
 }
-// Append one object (mesh m at pose P) to a state in place.
+// Append one object (mesh m at pose P) to each of n states in place, their
+// nearest points included.
+struct MsgAdd {
+    MeshDev m;
+    MsgState st;
+    const float *pose;        // 12 binary32 (device)
+    uint32_t *keys;           // W*H raster keys
+    int label;
+};
+constexpr int kMsgAdds = 8;
 struct MsgAddArgs {
     SceneDev s;
-    MeshDev m;
-    const float *pose;        // 12 binary32 (device)
-    int label;
-    MsgState st;
-    uint32_t *keys;           // W*H raster keys
-    int *flag;                // set to 1 when the object occludes the state (not monotone)
+    MsgAdd add[kMsgAdds];
+    int n;
+    int *flag;                // set to 1 when an object occludes its state (not monotone)
 };
-// Score every successor of one state: one object at each of n poses.
+// Successors of one state: one object at each of n poses.
+struct MsgItem {
+    MeshDev m;
+    MsgState st;
+    const float *poses;       // n * 12
+    int n, first;             // `first`: the item's first successor in the launch
+    int label;
+    int vbox[4];              // label volumes: x0, y0, w, h of the label's pixels
+    int32_t *valid, *jr, *jo, *nr, *nq;   // nr, nq may be null
+};
+// Score the successors of many states and objects of a scene in one launch.
 struct MsgArgs {
     SceneDev s;
-    MeshDev m;
-    const float *poses;       // n * 12
-    int n, label;
-    int vbox[4];              // label volumes: x0, y0, w, h of the label's pixels
-    MsgState st;
-    int32_t *valid, *jr, *jo, *nr, *nq;   // nr, nq may be null
-    int lds_words;            // dynamic LDS per work-group: the tile when it fits, then projected vertices
+    const MsgItem *items;     // n_items, ascending `first` (device)
+    int n_items, n;           // n: successors in all
+    int lds_words;            // dynamic LDS per work-group: the tile when it fits, then projected vertices or
+                              // the search's depth ranges and factors
     uint32_t *tiles;          // per work-group: W*H tile words (tiles larger than the LDS)
     int *cursor;              // pose cursor, zeroed by the launch
 };
 hipError_t upload_msg_colour_table(const float *lin256);
 hipError_t msg_state_clear(const SceneDev &s, const MsgState &st, hipStream_t stream);
 hipError_t msg_state_add(const MsgAddArgs &a, hipStream_t stream);
-// The per-observed-pixel nearest state point, after the last msg_state_add.
-hipError_t msg_state_near(const SceneDev &s, const MsgState &st, hipStream_t stream);
 hipError_t launch_msg(const MsgArgs &a, int grid, hipStream_t stream);
 hipError_t prepare_msg_kernel(int lds_per_group, int *lds_words);
 

@@ -368,25 +368,6 @@ __device__ __forceinline__ void mark_nn(uint32_t *bits, int nn, int W, int jx0, 
     if (jx >= 0 && jx < jw && jy >= 0 && jy < jh) Marks<KG>::set(bits, jy * jw + jx);
 }
 
-__device__ __forceinline__ int wave_popc(bool pred)
-{
-    return __popcll(__ballot(pred));
-}
-
-// Number of lanes below this one whose bit is set in mask m.
-__device__ __forceinline__ int lane_rank(unsigned long long m)
-{
-    return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-}
-
-// Make the LDS writes of a wave visible to all its lanes.
-__device__ __forceinline__ void wave_lds_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-}
-
 // Row of tile index k in a tile tw pixels wide (inv = 1 / tw in binary32).
 // An LDS tile holds fewer than 2^16 pixels: there (k + 1/2) / tw, whose
 // fraction lies at least 1 / (2 tw) from an integer, is computed with a

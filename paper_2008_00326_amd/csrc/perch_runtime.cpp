@@ -653,21 +653,21 @@ hipError_t enqueue(perch_ctx *ctx, const Work &w, const LaunchCfg &cfg, int pose
 }
 
 // Copy descriptors to the device through a pinned staging slot, asynchronously.
-perch_status upload(StreamBufs &sb, const Built &b, void *dev, hipStream_t st)
+perch_status upload(StreamBufs &sb, const void *src, size_t n, void *dev, hipStream_t st)
 {
     Staging &slot = sb.ring[sb.next];
     sb.next = (sb.next + 1) % 8;
     if (slot.done) HIP_TRY(hipEventSynchronize(slot.done));
     else HIP_TRY(hipEventCreateWithFlags(&slot.done, hipEventDisableTiming));
-    if (slot.bytes < b.bytes.size()) {
+    if (slot.bytes < n) {
         if (slot.host) HIP_TRY(hipHostFree(slot.host));
         slot.host = nullptr;
         slot.bytes = 0;
-        HIP_TRY(hipHostMalloc(&slot.host, b.bytes.size(), hipHostMallocDefault));
-        slot.bytes = b.bytes.size();
+        HIP_TRY(hipHostMalloc(&slot.host, n, hipHostMallocDefault));
+        slot.bytes = n;
     }
-    std::memcpy(slot.host, b.bytes.data(), b.bytes.size());
-    HIP_TRY(hipMemcpyAsync(dev, slot.host, b.bytes.size(), hipMemcpyHostToDevice, st));
+    std::memcpy(slot.host, src, n);
+    HIP_TRY(hipMemcpyAsync(dev, slot.host, n, hipMemcpyHostToDevice, st));
     HIP_TRY(hipEventRecord(slot.done, st));
     return PERCH_OK;
 }
@@ -695,7 +695,7 @@ perch_status run_direct(perch_ctx *ctx, const perch_work *req, int32_t n_req, hi
     const LaunchCfg cfg = launch_cfg(ctx);
     if (perch_status s = ensure_bufs(ctx, sb.lb, b.bytes.size(), b.n_poses, b.n_items, b.max_pixels, cfg, b.any_rgb))
         return s;
-    if (perch_status s = upload(sb, b, sb.lb.desc.ptr, st)) return s;
+    if (perch_status s = upload(sb, b.bytes.data(), b.bytes.size(), sb.lb.desc.ptr, st)) return s;
     const Work w = make_work(sb.lb, b, b.n_poses, cfg, b.max_pixels, want_best);
     sb.last_n = b.n_poses;
     hipError_t e = enqueue(ctx, w, cfg, b.n_poses, b.n_items, b.any_rgb, b.any_pv, st, true);
@@ -1594,17 +1594,20 @@ perch_status perch_refine_poses(perch_ctx *ctx, int32_t scene_id, int32_t mesh_i
 namespace {
 
 // Layout of a stream's tree buffer: cursor and flag, then the raster keys of
-// a composition, the placed poses, the per-work-group tiles and the scores.
+// a composition, the placed poses, the launch's items, the per-work-group
+// tiles and the scores.
 struct MsgLayout {
-    size_t keys, poses, tiles, out, bytes;
+    size_t keys, poses, items, tiles, out, bytes;
 };
-static MsgLayout msg_layout(size_t px, int grid, size_t n_poses, size_t n_out)
+// adds: objects appended at once (raster keys each)
+static MsgLayout msg_layout(size_t px, int grid, size_t adds, size_t n_poses, size_t n_items, size_t n_out)
 {
     auto up = [](size_t b) { return (b + 255) & ~(size_t)255; };
     MsgLayout l;
     l.keys = 512;
-    l.poses = l.keys + up(px * 4);
-    l.tiles = l.poses + up(n_poses * 12 * sizeof(float));
+    l.poses = l.keys + adds * up(px * 4);
+    l.items = l.poses + up(n_poses * 12 * sizeof(float));
+    l.tiles = l.items + up(n_items * sizeof(MsgItem));
     l.out = l.tiles + up((size_t)grid * px * 4);
     l.bytes = l.out + up(n_out * 3 * sizeof(int32_t));
     return l;
@@ -1617,24 +1620,45 @@ static perch_status msg_check_scene(const SceneRec &sr)
     return PERCH_OK;
 }
 
-static MsgArgs msg_args(perch_ctx *ctx, SceneRec &sr, const MeshRec &mr, int32_t label, const MsgState &st,
-                 const float *poses_dev, int n, char *base, const MsgLayout &l)
+static MsgItem msg_item(SceneRec &sr, const MeshRec &mr, int32_t label, const MsgState &st, const float *poses_dev,
+                        int n, int first)
 {
-    MsgArgs a{};
-    a.s = sr.dev;
+    MsgItem a{};
     a.m = mr.dev;
+    a.st = st;
     a.poses = poses_dev;
     a.n = n;
+    a.first = first;
     a.label = label;
     if ((sr.dev.flags & PERCH_VOL_MASK) == PERCH_VOL_LABEL) {
         const std::vector<int> lb = label_box(sr, label);
         for (int c = 0; c < 4; ++c) a.vbox[c] = lb[c];
     }
-    a.st = st;
+    return a;
+}
+
+// Write a launch's items and score their n successors.  A single item goes
+// by value through a kernel (no host memory is read later: the call can be
+// captured), more through a pinned staging slot.
+static perch_status msg_score(perch_ctx *ctx, StreamBufs &b, const SceneRec &sr, const std::vector<MsgItem> &items,
+                              int n, char *base, const MsgLayout &l, int grid, hipStream_t st)
+{
+    static_assert(sizeof(MsgItem) % 16 == 0 && sizeof(MsgItem) <= (size_t)kDescArgBytes, "one item by value");
+    if (items.size() == 1) {
+        HIP_TRY(launch_desc_write(items.data(), sizeof(MsgItem), base + l.items, st));
+    } else if (perch_status e = upload(b, items.data(), items.size() * sizeof(MsgItem), base + l.items, st)) {
+        return e;
+    }
+    MsgArgs a{};
+    a.s = sr.dev;
+    a.items = (const MsgItem *)(base + l.items);
+    a.n_items = (int)items.size();
+    a.n = n;
     a.lds_words = ctx->msg_lds_words;
     a.tiles = (uint32_t *)(base + l.tiles);
     a.cursor = (int *)base;
-    return a;
+    HIP_TRY(ctx->timed(kProfMsg, st, [&] { return launch_msg(a, std::min(grid, n), st); }));
+    return PERCH_OK;
 }
 
 }  // namespace
@@ -1666,7 +1690,7 @@ perch_status perch_msg_expand(perch_ctx *ctx, int32_t scene_id, const perch_plac
     const SceneDev &s = sr.dev;
     const size_t px = (size_t)s.W * s.H;
     const int grid = std::max(1, std::min(n, std::max(ctx->n_cu, 1)));
-    const MsgLayout l = msg_layout(px, grid, (size_t)n_state, 0);
+    const MsgLayout l = msg_layout(px, grid, 1, (size_t)n_state, 1, 0);
     if (perch_status e = ctx->ensure(b.msg, l.bytes)) return e;
     if (perch_status e = ctx->ensure(b.msg_states[0], msg_state_bytes(px))) return e;
     char *base = (char *)b.msg.ptr;
@@ -1683,28 +1707,25 @@ perch_status perch_msg_expand(perch_ctx *ctx, int32_t scene_id, const perch_plac
         for (int k = 0; k < n_state; ++k) {
             MsgAddArgs a{};
             a.s = s;
-            a.m = ctx->meshes[state[k].mesh_id].dev;
-            a.pose = dp + 12 * (size_t)k;
-            a.label = state[k].label;
-            a.st = ms;
-            a.keys = (uint32_t *)(base + l.keys);
+            a.n = 1;
+            a.add[0] = MsgAdd{ctx->meshes[state[k].mesh_id].dev, ms, dp + 12 * (size_t)k, (uint32_t *)(base + l.keys),
+                              state[k].label};
             a.flag = flag;
             HIP_TRY(msg_state_add(a, st));
         }
-        HIP_TRY(msg_state_near(s, ms, st));
         int hflag = 0;
         HIP_TRY(hipMemcpyAsync(&hflag, flag, sizeof(int), hipMemcpyDeviceToHost, st));
         HIP_TRY(hipStreamSynchronize(st));
         if (hflag) return fail(PERCH_EINVAL, "the state is not monotone: an object occludes one placed before it");
     }
     if (n > 0) {
-        MsgArgs a = msg_args(ctx, sr, mi->second, label, ms, poses_dev, n, base, l);
+        MsgItem a = msg_item(sr, mi->second, label, ms, poses_dev, n, 0);
         a.valid = valid_dev;
         a.jr = jr_dev;
         a.jo = jo_dev;
         a.nr = nr_dev;
         a.nq = nq_dev;
-        HIP_TRY(ctx->timed(kProfMsg, st, [&] { return launch_msg(a, grid, st); }));
+        if (perch_status e = msg_score(ctx, b, sr, {a}, n, base, l, grid, st)) return e;
     }
     ctx->mark_use(sr.uses, st);
     ctx->mark_use(mi->second.uses, st);
@@ -1743,7 +1764,7 @@ perch_status perch_msg_search(perch_ctx *ctx, int32_t scene_id, const perch_msg_
     const size_t px = (size_t)s.W * s.H;
     const size_t sb = msg_state_bytes(px);
     const bool rgb = (s.flags & PERCH_USE_RGB) != 0;
-    const int grid = std::max(1, std::min((int)std::max<size_t>(max_n, 1), std::max(ctx->n_cu, 1)));
+    const int cu = std::max(ctx->n_cu, 1);
 
     struct Node {
         int64_t cost;
@@ -1761,26 +1782,49 @@ perch_status perch_msg_search(perch_ctx *ctx, int32_t scene_id, const perch_msg_
         for (const Node &nd : cur)
             for (int o = 0; o < n_obj; ++o)
                 if (!(nd.placed >> o & 1u)) total += (size_t)objects[o].n_poses;
-        const MsgLayout l = msg_layout(px, grid, 0, total);
-        if (perch_status e = ctx->ensure(b.msg, l.bytes)) return e;
+        int grid = (int)std::min<size_t>(std::max<size_t>(total, 1), cu);
+        size_t adds = level + 1 < n_obj ? (beam > 0 ? std::min(beam, kMsgAdds) : kMsgAdds) : 1;
+        MsgLayout l = msg_layout(px, grid, adds, 0, cur.size() * (size_t)n_obj, total);
+        perch_status fit = ctx->ensure(b.msg, l.bytes);
+        if (fit == PERCH_ENOMEM) {     // fewer work-groups with tiles, one object appended at a time
+            grid = (int)std::min<size_t>(std::max<size_t>(max_n, 1), grid);
+            adds = 1;
+            l = msg_layout(px, grid, adds, 0, cur.size() * (size_t)n_obj, total);
+            fit = ctx->ensure(b.msg, l.bytes);
+        }
+        if (fit) return fit;
         char *base = (char *)b.msg.ptr;
         int32_t *outd = (int32_t *)(base + l.out);
         size_t off = 0;
+        // in launches of at most 2^30 successors (one, unless a beam is enormous)
+        std::vector<MsgItem> items;
+        int launched = 0;
+        auto flush = [&]() {
+            if (items.empty()) return PERCH_OK;
+            const perch_status e = msg_score(ctx, b, sr, items, launched, base, l, grid, st);
+            items.clear();
+            launched = 0;
+            return e;
+        };
         for (size_t c = 0; c < cur.size(); ++c) {
             const MsgState ms = msg_state_at((char *)b.msg_states[cur_buf].ptr + c * sb, px, rgb);
             for (int o = 0; o < n_obj; ++o) {
                 if (cur[c].placed >> o & 1u) continue;
                 const int n = objects[o].n_poses;
                 if (n == 0) continue;
-                MsgArgs a = msg_args(ctx, sr, ctx->meshes[objects[o].mesh_id], objects[o].label, ms,
-                                     objects[o].poses_dev, n, base, l);
+                if ((long long)launched + n > (1LL << 30))
+                    if (perch_status e = flush()) return e;
+                MsgItem a = msg_item(sr, ctx->meshes[objects[o].mesh_id], objects[o].label, ms, objects[o].poses_dev,
+                                     n, launched);
                 a.valid = outd + off;
                 a.jr = outd + total + off;
                 a.jo = outd + 2 * total + off;
-                HIP_TRY(ctx->timed(kProfMsg, st, [&] { return launch_msg(a, std::min(grid, n), st); }));
+                items.push_back(a);
+                launched += n;
                 off += (size_t)n;
             }
         }
+        if (perch_status e = flush()) return e;
         std::vector<int32_t> h(3 * total);
         if (total > 0) HIP_TRY(hipMemcpyAsync(h.data(), outd, h.size() * sizeof(int32_t), hipMemcpyDeviceToHost, st));
         HIP_TRY(hipStreamSynchronize(st));
@@ -1834,21 +1878,22 @@ perch_status perch_msg_search(perch_ctx *ctx, int32_t scene_id, const perch_msg_
             return fail(PERCH_ENOMEM, "exhaustive search: %zu states of %zu bytes exceed the budget", keep, sb);
         if (perch_status e = ctx->ensure(b.msg_states[nb], keep * sb)) return e;
         char *base2 = (char *)b.msg.ptr;
-        for (size_t c = 0; c < keep; ++c) {
-            char *dst = (char *)b.msg_states[nb].ptr + c * sb;
-            HIP_TRY(hipMemcpyAsync(dst, (char *)b.msg_states[cur_buf].ptr + (size_t)cand[c].parent * sb, sb,
-                                   hipMemcpyDeviceToDevice, st));
-            const MsgState ms = msg_state_at(dst, px, rgb);
+        const size_t key_bytes = (px * 4 + 255) & ~(size_t)255;
+        for (size_t c0 = 0; c0 < keep; c0 += adds) {
             MsgAddArgs a{};
             a.s = s;
-            a.m = ctx->meshes[objects[cand[c].o].mesh_id].dev;
-            a.pose = objects[cand[c].o].poses_dev + 12 * (size_t)cand[c].k;
-            a.label = objects[cand[c].o].label;
-            a.st = ms;
-            a.keys = (uint32_t *)(base2 + l.keys);
+            a.n = (int)std::min(adds, keep - c0);
             a.flag = (int *)(base2 + 256);
+            for (int k = 0; k < a.n; ++k) {
+                const Cand &cd = cand[c0 + k];
+                char *dst = (char *)b.msg_states[nb].ptr + (c0 + k) * sb;
+                HIP_TRY(hipMemcpyAsync(dst, (char *)b.msg_states[cur_buf].ptr + (size_t)cd.parent * sb, sb,
+                                       hipMemcpyDeviceToDevice, st));
+                a.add[k] = MsgAdd{ctx->meshes[objects[cd.o].mesh_id].dev, msg_state_at(dst, px, rgb),
+                                  objects[cd.o].poses_dev + 12 * (size_t)cd.k,
+                                  (uint32_t *)(base2 + l.keys + k * key_bytes), objects[cd.o].label};
+            }
             HIP_TRY(msg_state_add(a, st));
-            HIP_TRY(msg_state_near(s, ms, st));
         }
         cur.swap(next);
         cur_buf = nb;

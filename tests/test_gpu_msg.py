@@ -132,6 +132,33 @@ def test_search_matches_oracle(ctx, beam, flags):
     assert got == exp, (got, exp)
 
 
+@pytest.mark.parametrize("flags", [oracle.MARK_OCCLUDERS, oracle.USE_RGB | oracle.VOL_LABEL])
+@pytest.mark.parametrize("delta", [1.5, 60.0])
+def test_search_windows_of_one_tile_and_of_several_blocks(ctx, flags, delta):
+    """J_o windows within a 4x4 pixel tile, and over more than 8x8 of them
+    (delta 60 mm at 0.8 m and f = 300: some 49 pixels), from the root and
+    from a state whose points compete with the successor's own."""
+    meshes, scene, gt, cands = _world(seed=3)
+    rgb = bool(flags & oracle.USE_RGB)
+    kw = dict(delta_mm=delta, tau_c=20.0, flags=flags)
+    say(f"msg windows: flags {flags}, delta {delta}")
+    sid = ctx.set_scene(scene.K, scene.depth, scene.rgb, scene.labels, **kw)
+    mids = [ctx.load_mesh(m.xyz, m.tri, m.rgb) for m in meshes]
+    checked = 0
+    for seq in ((), ((0, 0),), ((2, 1),)):
+        ostate = [(meshes[o], o + 1, cands[o][k]) for o, k in seq]
+        gstate = [(mids[o], o + 1, cands[o][k]) for o, k in seq]
+        for o in {0, 1, 2} - {o for o, _ in seq}:
+            got = ctx.msg_expand(sid, gstate, mids[o], _cuda(cands[o]), label=o + 1)
+            exp = oracle.msg_expand(scene, ostate, meshes[o], cands[o], label=o + 1, threads=THREADS, **kw)
+            check_edges(got, exp, rgb, f"delta {delta} state {seq} object {o}")
+            checked += int(exp[0].sum())
+    for m in mids:
+        ctx.unload_mesh(m)
+    ctx.drop_scene(sid)
+    assert checked >= 8
+
+
 def _random_world(seed):
     """Three boxes of random sizes at random nearby table positions and yaws
     (some touching or hiding one another), each with four random candidates
