@@ -424,12 +424,14 @@ perch_status perch_msg_search(perch_ctx *ctx, int32_t scene_id, const perch_msg_
  * 8 ICP refinement, 9 tree successors, 10 kNN I distances and reductions,
  * 11 a prepared batch's whole graph replay (perch_batch_launch: descriptor
  * upload, set-up, the four scoring classes, argmin, result download; the
- * kernels inside a graph are not bracketed one by one). */
+ * kernels inside a graph are not bracketed one by one), 12 launches of few
+ * poses scored by many work-groups each (their set-up included). */
 perch_status perch_profile_enable(perch_ctx *ctx, int32_t enable);
 perch_status perch_profile_read(perch_ctx *ctx, int32_t n_slots, double *total_ms, int32_t *launches);
 
 /* Footprint class (0..3, the scoring slots 1..4 of the profiler) that the
- * last perch_score_poses call on hip_stream assigned to each of its n poses:
+ * last perch_score_poses call on hip_stream assigned to each of its n poses
+ * (a launch of few poses, slot 12, assigns them too):
  * class_host[i] for pose i.  Blocks until that call has finished.  Meant for
  * inspection and work accounting. */
 perch_status perch_last_classes(perch_ctx *ctx, void *hip_stream, int32_t n, int32_t *class_host);
@@ -451,6 +453,8 @@ perch_status perch_last_classes(perch_ctx *ctx, void *hip_stream, int32_t n, int
  *   key_bands:    for poses whose J_o keys do not fit in LDS beside the
  *                 raster tile: 1 = keys in device memory, 2 = keys in LDS,
  *                 one band of rows at a time (0 = 2).
+ * With any of these set, launches of few poses go through the footprint
+ * classes too instead of spreading each pose over many work-groups.
  * The setting applies to launches enqueued afterwards, and to batches
  * created afterwards (a batch keeps the setting it was created with).
  * NULL restores the defaults.  perch_get_tuning returns the values in force,

@@ -360,7 +360,7 @@ class Context:
                 "key_bands": t.key_bands}
 
     PROFILE_SLOTS = ("setup", "score_lds_small", "score_lds_large", "score_lds_tile", "score_device", "argmin",
-                     "scene_prep", "render", "icp", "msg", "knn1", "batch_graph")
+                     "scene_prep", "render", "icp", "msg", "knn1", "batch_graph", "score_wide")
 
     def profile(self, enable: bool = True):
         """Start (clearing the record) or stop bracketing kernel launches with HIP events."""

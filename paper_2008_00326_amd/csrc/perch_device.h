@@ -456,6 +456,57 @@ __device__ __forceinline__ float window_inv(int z, float dl)
     return den > 1.0f ? 1.0f / den : INFINITY;
 }
 
+// Search for the rendered point nearest to observed point o of pixel (i, j)
+// among the points of a tile (tw x th > 0 pixels at (tx0, ty0)) in blocks of
+// 4x4 pixels: `scan(b)` visits the points of block b (row-major) and lowers
+// `bd2`, the least squared distance so far (above dq^2: none), in which a
+// caller may start with a bound of its own; `range(b)` is the depth range of
+// the block's points, least | greatest << 16, 65535 | 0 without any.  The
+// block of the pixel itself, or the nearest one, goes first; then the window
+// shrinks to what can still be nearer, and its blocks go by their depth
+// ranges.  `any`: the first point within delta ends the search.
+template <class Range, class Scan>
+__device__ __forceinline__ void nearest_rendered(const SceneDev &s, int3 o, int i, int j, int tx0, int ty0, int tw,
+                                                 int th, bool any, const int &bd2, Range range, Scan scan)
+{
+    const int bw = (tw + 3) >> 2;
+    const int xc = min(max(i - tx0, 0), tw - 1) >> 2, yc = min(max(j - ty0, 0), th - 1) >> 2;
+    auto near_enough = [&](int b) {
+        const uint32_t r = range(b);
+        const int dz = max(max(16 * (int)(r & 0xFFFFu) - o.z, o.z - 16 * (int)(r >> 16)), 0);
+        return dz <= s.dq && __mul24(dz, dz) <= bd2;
+    };
+    if (near_enough(yc * bw + xc)) scan(yc * bw + xc);
+    if (any && bd2 <= s.dq2) return;
+    // pixels that can hold a point at most the best's distance away: the
+    // neighbour window of radius e in place of delta + 1/4 (the factor covers
+    // the binary32 rounding)
+    const float dlw = s.delta + 0.25f;
+    const float e = bd2 > s.dq2 ? dlw : fminf((float)((int)sqrtf((float)bd2) + 1) * 0.0625f + 0.25f, dlw);
+    const float iz = window_inv(o.z >> 4, e), f = e / dlw * 1.000004f;
+    const int wu = window_half(gld(s.ax + i) * f, iz, s.W), wv = window_half(gld(s.ay + j) * f, iz, s.H);
+    const int i0 = max(i - wu - tx0, 0), i1 = min(i + wu - tx0, tw - 1);
+    const int j0 = max(j - wv - ty0, 0), j1 = min(j + wv - ty0, th - 1);
+    if (i0 > i1 || j0 > j1) return;
+    const int bx1 = i1 >> 2, by1 = j1 >> 2;
+    // squares of 8x8 blocks, one bit each
+    for (int by = j0 >> 2; by <= by1; by += 8)
+        for (int bx = i0 >> 2; bx <= bx1; bx += 8) {
+            unsigned long long mask = 0;
+            for (int y = 0; y < 8 && by + y <= by1; ++y)
+                for (int x = 0; x < 8 && bx + x <= bx1; ++x)
+                    if (near_enough((by + y) * bw + bx + x)) mask |= 1ULL << (8 * y + x);
+            if (yc >= by && yc < by + 8 && xc >= bx && xc < bx + 8) mask &= ~(1ULL << (8 * (yc - by) + xc - bx));
+            while (mask) {
+                const int k = __ffsll(mask) - 1, b = (by + (k >> 3)) * bw + bx + (k & 7);
+                mask &= mask - 1;
+                if (!near_enough(b)) continue;
+                scan(b);
+                if (any && bd2 <= s.dq2) return;
+            }
+        }
+}
+
 // ------------------------------------------------------------------ integer helpers
 
 // Row of entry q of a row-major window ww pixels wide: a binary32 estimate

@@ -142,6 +142,11 @@ hipError_t launch_hash_build(const SceneDev &s, int *count, long long *blk, hipS
 // classes, then the per-item argmin if w.best is set.
 hipError_t launch_setup(const Work &w, int poses_grid, hipStream_t st);
 hipError_t launch_score_class(const Work &w, const LaunchCfg &c, int cls, bool any_rgb, bool any_pv, hipStream_t st);
+// The wide path of a launch of few poses: the raster and the scoring of each
+// pose spread over many work-groups, its tile in a device-memory slot of
+// `dev_tile_words` words at gscratch; `bands` work-groups score each pose.
+// Replaces launch_setup and launch_score_class; the same results.
+hipError_t launch_wide(const Work &w, int n_poses, int max_tris, int bands, bool any_rgb, bool any_pv, hipStream_t st);
 hipError_t launch_item_argmin(const Work &w, int items_grid, hipStream_t st);
 // Descriptor block of a launch written by a kernel that takes the bytes by
 // value (no host staging); at most kDescArgBytes bytes.
@@ -292,7 +297,7 @@ hipError_t knn1_score(const Knn1Args &a, int p, int L, hipStream_t st);
 
 // Kernel slots reported by the profiler (perch_profile_read).
 enum ProfSlot { kProfSetup = 0, kProfClass0 = 1, kProfArgmin = 5, kProfScenePrep = 6, kProfRender = 7,
-                kProfIcp = 8, kProfMsg = 9, kProfKnn1 = 10, kProfGraph = 11, kNumProfSlots = 12 };
+                kProfIcp = 8, kProfMsg = 9, kProfKnn1 = 10, kProfGraph = 11, kProfWide = 12, kNumProfSlots = 13 };
 hipError_t launch_render(const SceneDev &s, const MeshDev &m, const float *poses, int n,
                          uint32_t *keys, uint16_t *depth, uint8_t *rgb, int32_t *tri,
                          hipStream_t st);

@@ -58,16 +58,24 @@ template <> struct KeyOf<true> {
     __device__ static void store(T *p, T v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 };
 
+// 64-bit keys in LDS (the wide path: no limit on distance or index).
+struct KeyWide {
+    using T = unsigned long long;
+    static constexpr T kEmpty = ~0ULL;
+    __device__ static T make(int d2, int k) { return ((unsigned long long)(uint32_t)d2 << 32) | (uint32_t)k; }
+    __device__ static int index(T key) { return (int)(key & 0xFFFFFFFFu); }
+    __device__ static void min(T *p, T v) { atomicMin(p, v); }
+};
+
 // Key update of an observed point q by rendered point (X, Y, Z) with tile
 // index k, if the two lie within delta.  The three offsets saturate to 16
 // bits (v_cvt_pk_i16_i32) and two v_dot2_i32_i16 sum their squares: at most
 // 3 * 2^30 < 2^32, so the sum read unsigned is exact when no offset
 // saturated and exceeds dq^2 (dq < 2^13) when one did.
 typedef short perch_s2 __attribute__((ext_vector_type(2)));
-template <bool G>
-__device__ __forceinline__ void mark_one(int3 q, int X, int Y, int Z, int k, int dq2, typename KeyOf<G>::T *key)
+template <class K>
+__device__ __forceinline__ void mark_one(int3 q, int X, int Y, int Z, int k, int dq2, typename K::T *key)
 {
-    using K = KeyOf<G>;
     const perch_s2 xy = __builtin_amdgcn_cvt_pk_i16(q.x - X, q.y - Y);
     const perch_s2 z0 = __builtin_amdgcn_cvt_pk_i16(q.z - Z, 0);
     const uint32_t d2 = (uint32_t)__builtin_amdgcn_sdot2(xy, xy, __builtin_amdgcn_sdot2(z0, z0, 0, false), false);
@@ -141,9 +149,9 @@ __device__ __forceinline__ MarkScene mark_scene(const SceneDev &s)
 // four rounds per iteration; a wider one in row-major order, four pixels
 // per lane per round.  Image and key offsets are 32-bit, products 24-bit
 // (every index here is below 2^24).
-template <bool G>
+template <class K>
 __device__ void wave_mark(const MarkScene &s, int i, int j, int d, int k, int X, int Y, int wuv,
-                          typename KeyOf<G>::T *keys, int jx0, int jy0, int jw, int jh, int lane)
+                          typename K::T *keys, int jx0, int jy0, int jw, int jh, int lane)
 {
     const int wu = wuv & 0xFFFF, wv = wuv >> 16;
     const int i0 = max(max(i - wu, 0), jx0), i1 = min(min(i + wu, s.W - 1), jx0 + jw - 1);
@@ -163,7 +171,7 @@ __device__ void wave_mark(const MarkScene &s, int i, int j, int d, int k, int X,
         // exactly for q < 256
         const uint32_t rc = c_rcp16[ww];
         const int4 *wopt = s.opt + pbase;
-        typename KeyOf<G>::T *wkey = keys + kbase;
+        typename K::T *wkey = keys + kbase;
         int3 q[4];
         int kk[4];
 #pragma unroll
@@ -177,7 +185,7 @@ __device__ void wave_mark(const MarkScene &s, int i, int j, int d, int k, int X,
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u)
-            if (64 * u + lane < ws) mark_one<G>(q[u], X, Y, Z, k, dq2, wkey + kk[u]);
+            if (64 * u + lane < ws) mark_one<K>(q[u], X, Y, Z, k, dq2, wkey + kk[u]);
         return;
     }
     if (ww <= 64) {
@@ -194,7 +202,7 @@ __device__ void wave_mark(const MarkScene &s, int i, int j, int d, int k, int X,
 #pragma unroll
             for (int u = 0; u < 4; ++u) q[u] = opt_at(s.opt, (uint32_t)(pix + u * step));
 #pragma unroll
-            for (int u = 0; u < 4; ++u) mark_one<G>(q[u], X, Y, Z, k, dq2, keys + kk + u * kstep);
+            for (int u = 0; u < 4; ++u) mark_one<K>(q[u], X, Y, Z, k, dq2, keys + kk + u * kstep);
             pix += 4 * step;
             kk += 4 * kstep;
         }
@@ -204,7 +212,7 @@ __device__ void wave_mark(const MarkScene &s, int i, int j, int d, int k, int X,
             q[u] = row + u * rows < wh ? opt_at(s.opt, (uint32_t)(pix + u * step)) : make_int3(0, 0, kNoPoint);
 #pragma unroll
         for (int u = 0; u < 3; ++u)
-            if (row + u * rows < wh) mark_one<G>(q[u], X, Y, Z, k, dq2, keys + kk + u * kstep);
+            if (row + u * rows < wh) mark_one<K>(q[u], X, Y, Z, k, dq2, keys + kk + u * kstep);
         return;
     }
     const float inv = 1.0f / (float)ww;
@@ -220,7 +228,7 @@ __device__ void wave_mark(const MarkScene &s, int i, int j, int d, int k, int X,
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u)
-            if (q0 + 64 * u + lane < ws) mark_one<G>(qv[u], X, Y, Z, k, dq2, keys + kk[u]);
+            if (q0 + 64 * u + lane < ws) mark_one<K>(qv[u], X, Y, Z, k, dq2, keys + kk[u]);
     }
 }
 
@@ -250,10 +258,12 @@ constexpr int kLanesMin = 32;
 // lanes' neighbour ellipses (E: mark_ellipse; c2 = (fx/fy)^2), which holds
 // every lane's own.  Queued inliers come from neighbouring tile pixels, so
 // one offset's loads and key updates fall on neighbouring pixels.  Offsets
-// outside a lane's window re-read a pixel of it and mark nothing.
-template <bool G>
+// outside a lane's window re-read a pixel of it and mark nothing.  Waves that
+// share the inliers take every rows-th row of offsets from row0 on.
+template <class K>
 __device__ void wave_mark_lanes(const MarkScene &s, bool act, int i, int j, int d, int k, int X, int Y, int wuv,
-                                float E, float c2, typename KeyOf<G>::T *keys, int jx0, int jy0, int jw, int jh)
+                                float E, float c2, typename K::T *keys, int jx0, int jy0, int jw, int jh,
+                                int row0 = 0, int rows = 1)
 {
     const int wu = wuv & 0xFFFF, wv = wuv >> 16;
     int x0 = max(max(-wu, -i), jx0 - i), x1 = min(min(wu, s.W - 1 - i), jx0 + jw - 1 - i);
@@ -271,7 +281,7 @@ __device__ void wave_mark_lanes(const MarkScene &s, bool act, int i, int j, int 
     const int dq2 = s.dq2;
     const int pix = live ? j * s.W + i : 0;
     const int kp = (j - jy0) * jw + (i - jx0);
-    for (int dy = DY0; dy <= DY1; ++dy) {
+    for (int dy = DY0 + row0; dy <= DY1; dy += rows) {
         // the chord's half-width, rounded up past the binary32 error (the
         // row term lowered by 1e-5 relative, the root raised)
         const float t = Em - c2 * (float)(dy * dy) * 0.99999f;
@@ -291,7 +301,7 @@ __device__ void wave_mark_lanes(const MarkScene &s, bool act, int i, int j, int 
             }
 #pragma unroll
             for (int u = 0; u < 4; ++u)
-                if (rowok && cx[u] == dx + u) mark_one<G>(qv[u], X, Y, Z, k, dq2, keys + krow + cx[u]);
+                if (rowok && cx[u] == dx + u) mark_one<K>(qv[u], X, Y, Z, k, dq2, keys + krow + cx[u]);
         }
     }
 }
@@ -383,7 +393,7 @@ __device__ __forceinline__ int tile_row(int k, int tw, float inv)
 // ------------------------------------------------------------------ per pose
 
 template <int BLOCK, bool G, bool KG, bool RGB, bool PV>
-__device__ void score_pose(const Work &w, int p, uint32_t *tile, typename KeyOf<KG>::T *keys, float4 *labs, int *cnt,
+__device__ __forceinline__ void score_pose(const Work &w, int p, uint32_t *tile, typename KeyOf<KG>::T *keys, float4 *labs, int *cnt,
                            int2 *wq)
 {
     using K = KeyOf<KG>;
@@ -549,10 +559,10 @@ __device__ void score_pose(const Work &w, int p, uint32_t *tile, typename KeyOf<
                 if (n >= kLanesMin) {
                     const float E = lane < n ? mark_ellipse(s, ei, ej, ed) : 0.0f;
                     const float c2 = (s.fx / s.fy) * (s.fx / s.fy);
-                    wave_mark_lanes<KG>(ms, lane < n, ei, ej, ed, kk, X, Y, wuv, E, c2, keys, in.jx0, by0, in.jw, bh);
+                    wave_mark_lanes<K>(ms, lane < n, ei, ej, ed, kk, X, Y, wuv, E, c2, keys, in.jx0, by0, in.jw, bh);
                 } else {
                     for (int t = 0; t < n; ++t)
-                        wave_mark<KG>(ms, __builtin_amdgcn_readlane(ei, t), __builtin_amdgcn_readlane(ej, t),
+                        wave_mark<K>(ms, __builtin_amdgcn_readlane(ei, t), __builtin_amdgcn_readlane(ej, t),
                                       __builtin_amdgcn_readlane(ed, t), __builtin_amdgcn_readlane(kk, t),
                                       __builtin_amdgcn_readlane(X, t), __builtin_amdgcn_readlane(Y, t),
                                       __builtin_amdgcn_readlane(wuv, t), keys, in.jx0, by0, in.jw, bh, lane);
@@ -812,9 +822,17 @@ __device__ __forceinline__ int cost_bucket(int tile_px, int j_px, int nt)
 }
 
 // Regions and footprint class of global pose p; returns its order key
-// (class * kNumStrips + strip) * kNumBuckets + sub-key.
-__device__ int classify_pose(const Work &w, int p)
+// (class * kNumStrips + strip) * kNumBuckets + sub-key.  WAVE: by a whole wave
+// (`lane`: the thread's lane), which shortens the chain of binary64 divisions
+// of a single pose; with a thread per pose a launch of thousands takes less.
+template <bool WAVE>
+__device__ int classify_pose(const Work &w, int p, int lane, PoseInfo &in)
 {
+    auto project = [&](const float *P, const MeshDev &m, double pad, const SceneDev &s, double *umin, double *umax,
+                       double *vmin, double *vmax, double *zmin, double *zmax) {
+        if constexpr (WAVE) project_box_wave(P, m.lo, m.hi, pad, s, lane, umin, umax, vmin, vmax, zmin, zmax);
+        else project_box(P, m.lo, m.hi, pad, s, umin, umax, vmin, vmax, zmin, zmax);
+    };
     // the item holding global pose p: the last one with first <= p
     int lo = 0, hi = w.hdr->n_items - 1;
     while (lo < hi) {
@@ -827,12 +845,11 @@ __device__ int classify_pose(const Work &w, int p)
     const MeshDev &m = w.meshes[it.mesh];
     float P[12];
     for (int k = 0; k < 12; ++k) P[k] = it.poses[12 * (size_t)(p - it.first) + k];
-    PoseInfo in;
     in.item = lo;
     in.local = p - it.first;
     double umin, umax, vmin, vmax, zmin, zmax;
     // Raster tile: every drawn vertex has Zc >= 100 and lies in the AABB.
-    project_box(P, m.lo, m.hi, 0.0, s, &umin, &umax, &vmin, &vmax, &zmin, &zmax);
+    project(P, m, 0.0, s, &umin, &umax, &vmin, &vmax, &zmin, &zmax);
     if (zmin >= 100.0) {
         clip_box(umin, umax, vmin, vmax, s.W, s.H, &in.tx0, &in.ty0, &in.tw, &in.th);
     } else if (zmax < 99.999) {
@@ -849,7 +866,7 @@ __device__ int classify_pose(const Work &w, int p)
         in.vw = it.vbox[2];
         in.vh = it.vbox[3];
     } else {
-        project_box(P, m.lo, m.hi, (double)s.delta + 0.5, s, &umin, &umax, &vmin, &vmax, &zmin, &zmax);
+        project(P, m, (double)s.delta + 0.5, s, &umin, &umax, &vmin, &vmax, &zmin, &zmax);
         if (zmin > 0.5) {
             clip_box(umin, umax, vmin, vmax, s.W, s.H, &in.vx0, &in.vy0, &in.vw, &in.vh);
         } else if (zmax <= 0.0) {
@@ -869,7 +886,6 @@ __device__ int classify_pose(const Work &w, int p)
     in.jw = (in.tw > 0 && jx1 >= in.jx0) ? jx1 - in.jx0 + 1 : 0;
     in.jh = (in.th > 0 && jy1 >= in.jy0) ? jy1 - in.jy0 + 1 : 0;
     if (in.jw == 0 || in.jh == 0) in.jw = in.jh = 0;
-    w.info[p] = in;
     // LDS words: tile + 32-bit keys; 32-bit keys need d2 < 2^16 and tile
     // indices < 2^16, otherwise the pose is scored from device memory
     // (J_o by nearest-neighbour marking: a bitmap, one bit per pixel, with
@@ -888,9 +904,8 @@ __device__ int classify_pose(const Work &w, int p)
     // at a time
     const int ns = w.hdr->n_scenes;
     const int sub = ns > 1 ? (it.scene * kNumBuckets) / ns : kNumBuckets - 1 - cost_bucket(tile_words, in.jw * in.jh, m.nt);
-    const int order = (cls * kNumStrips + strip) * kNumBuckets + sub;
-    w.info[p].order = order;
-    return order;
+    in.order = (cls * kNumStrips + strip) * kNumBuckets + sub;
+    return in.order;
 }
 
 // Classify every pose.  Counts are gathered per work-group in LDS and added
@@ -906,7 +921,9 @@ __global__ __launch_bounds__(256) void setup_kernel(Work w)
     __syncthreads();
     int order = -1, local = 0;
     if (p < w.hdr->n_poses) {
-        order = classify_pose(w, p);
+        PoseInfo in;
+        order = classify_pose<false>(w, p, 0, in);
+        w.info[p] = in;
         if (w.sort) atomicAdd(&lcnt[order], 1);
         else local = atomicAdd(&lcls[order / (kNumStrips * kNumBuckets)], 1);
     }
@@ -979,6 +996,302 @@ __global__ __launch_bounds__(256) void order_kernel(Work w)
     if (valid) {
         const int cls = order / (kNumStrips * kNumBuckets);
         w.lists[cls * w.cap_poses + base[order] + lbase[order] + local] = p;
+    }
+}
+
+// ------------------------------------------------------------------ few poses
+
+// The wide path: a launch of few poses leaves most of the chip idle when a
+// work-group scores a whole pose, and lasts as long as its slowest pose
+// (0.29 ms for one near the truth, most of it marking).  Here a pose's
+// triangles go to as many work-groups as they fill, min-combined into a tile
+// in device memory, and its image rows are then cut into bands that
+// work-groups score side by side: a band's group counts the rendered points
+// of its own rows and, for the J_o keys of those rows (64 bits, in LDS), also
+// marks from the rows within the neighbour window above and below.  No group
+// waits for another; the counts meet in the outputs.
+//
+// One wave marks from 64 inliers in some 15 us, so a band's list of inliers
+// is shared out over its group's waves, by window rows where chunks are few.
+// Measured and slower (one pose of 2k triangles / 5 objects of 32 candidates,
+// scoring alone, us): a list per wave 160 / 367; marks into device memory
+// instead of bands 96 / 214, or through LDS 54 / 146 but 105 for 167 poses
+// against 78 (device-scope updates run at some 13 G/s); a search by each
+// observed point over the inliers' 4x4 pixel blocks 208 / 229.
+
+// Regions of each pose, its outputs and its tile cleared; a group per pose.
+__global__ __launch_bounds__(256) void wide_setup_kernel(Work w)
+{
+    const int p = blockIdx.x, tid = threadIdx.x;
+    if (p >= w.hdr->n_poses) return;
+    PoseInfo in;
+    (void)classify_pose<true>(w, p, tid & 63, in);     // every wave its own copy
+    if (tid == 0) {
+        w.info[p] = in;
+        const ItemDev &it = w.items[in.item];
+        it.jr[in.local] = 0;
+        it.jo[in.local] = 0;
+        if (it.nr) it.nr[in.local] = 0;
+        if (it.nq) it.nq[in.local] = 0;
+    }
+    uint32_t *tile = w.gscratch + (size_t)p * w.dev_tile_words;
+    const int tpx = in.tw * in.th;
+    // slots start at even words: pairs, the last one past an odd tile within its slot
+    for (int k = 2 * tid; k < tpx; k += 512) *reinterpret_cast<uint2 *>(tile + k) = make_uint2(kEmptyKey, kEmptyKey);
+}
+
+// One thread per (triangle, pose).
+__global__ __launch_bounds__(256) void wide_raster_kernel(Work w)
+{
+    const int p = blockIdx.y;
+    if (p >= w.hdr->n_poses) return;
+    const PoseInfo in = w.info[p];
+    const ItemDev &it = w.items[in.item];
+    const MeshDev &m = w.meshes[it.mesh];
+    const int t = blockIdx.x * 256 + threadIdx.x;
+    if (t >= m.nt || in.tw == 0 || in.th == 0) return;
+    float P[12];
+#pragma unroll
+    for (int k = 0; k < 12; ++k) P[k] = it.poses[12 * (size_t)in.local + k];
+    raster_triangle<true>(w.scenes[it.scene], m, P, t, in.tx0, in.ty0, in.tw, in.th,
+                          w.gscratch + (size_t)p * w.dev_tile_words);
+}
+
+constexpr int kWideBlock = 512;
+constexpr int kWideKeys = 4352;     // 64-bit LDS keys of a band: at least one row (images are at most 4096 wide)
+constexpr int kWideList = 2048;
+
+template <bool RGB, bool PV>
+__global__ __launch_bounds__(kWideBlock, 4) void wide_score_kernel(Work w)
+{
+    constexpr int NW = kWideBlock / 64;
+    __shared__ unsigned long long keys[kWideKeys];
+    __shared__ int2 wq[NW * 128];
+    __shared__ int cnt[4];
+    __shared__ int list[kWideList];     // tile indices of inliers to mark from
+    __shared__ int s_n;
+    using K = KeyWide;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int p = blockIdx.y;
+    if (p >= w.hdr->n_poses) return;
+    const PoseInfo in = w.info[p];
+    const ItemDev &it = w.items[in.item];
+    const SceneDev &s = w.scenes[it.scene];
+    const MeshDev &m = w.meshes[it.mesh];
+    const uint32_t *tile = w.gscratch + (size_t)p * w.dev_tile_words;
+    const bool rgb = RGB && (s.flags & 1u) != 0;
+    const bool mark = (s.flags & 2u) != 0;
+    const bool label_mode = (s.flags & (3u << 4)) == (2u << 4);
+    const bool cyl = (s.flags & (3u << 4)) == (1u << 4);
+    const bool nnm = PV && (s.flags & 64u) != 0;       // J_o by nearest-neighbour marking
+    const bool knn2 = PV && (s.flags & 128u) != 0;     // J_r neighbours by the kNN II scan
+    const bool hsh = PV && (s.flags & kHashFlag) != 0; // J_r neighbours through the voxel hash
+    const bool ocol = rgb && !nnm;
+    uint32_t *bits = reinterpret_cast<uint32_t *>(keys);
+    // image rows with work: of the tile and of the V region
+    const int u0 = in.th == 0 ? in.vy0 : (in.vh == 0 ? in.ty0 : min(in.ty0, in.vy0));
+    const int u1 = in.th == 0 ? in.vy0 + in.vh : (in.vh == 0 ? in.ty0 + in.th : max(in.ty0 + in.th, in.vy0 + in.vh));
+    const int hb = max(1, min((u1 - u0 + (int)gridDim.x - 1) / (int)gridDim.x, kWideKeys / max(in.jw, 1)));
+    if (u0 + (int)blockIdx.x * hb >= u1) return;
+    float P[12];
+#pragma unroll
+    for (int k = 0; k < 12; ++k) P[k] = it.poses[12 * (size_t)in.local + k];
+    const MarkScene ms = mark_scene(s);
+    const double dl = (double)s.delta;
+    const float tinv = 1.0f / (float)max(in.tw, 1);
+    int2 *const q = wq + wave * 128;
+    if (tid < 4) cnt[tid] = 0;
+    if (tid == 0) s_n = 0;
+    int cL = 0, cR = 0, cQ = 0, cO = 0;
+    for (int y0 = u0 + (int)blockIdx.x * hb; y0 < u1; y0 += (int)gridDim.x * hb) {
+        const int y1 = min(y0 + hb, u1);
+        // J_o rows of the band, their keys, and the tile rows to visit: the
+        // band's own and those whose points reach its J_o rows
+        const int by0 = max(y0, in.jy0), bh = in.jw > 0 ? max(min(y1, in.jy0 + in.jh) - by0, 0) : 0;
+        const int bpx = in.jw * bh;
+        int ra = max(y0, in.ty0), rb = min(y1, in.ty0 + in.th);
+        if (bpx > 0) {
+            const int ha = max(by0 - s.wty, in.ty0), hz = min(by0 + bh + s.wty, in.ty0 + in.th);
+            if (ha < hz) {
+                ra = ra < rb ? min(ra, ha) : ha;
+                rb = max(rb, hz);
+            }
+        }
+        __syncthreads();      // the last band's keys have been read
+        if (nnm) {
+            for (int k = tid; k < (bpx + 31) >> 5; k += kWideBlock) bits[k] = 0u;
+        } else {
+            for (int k = tid; k < bpx; k += kWideBlock) keys[k] = K::kEmpty;
+        }
+        __syncthreads();
+        // colour test (Eq. 4) of queued inliers
+        auto flush_r = [&](int n) {
+            wave_lds_sync();
+            bool out = false, own = false;
+            if (lane < n) {
+                const int2 e = q[lane];
+                const uint32_t key = gld(tile + e.x);
+                const int ty = window_row(e.x, in.tw, tinv), i = in.tx0 + e.x - ty * in.tw, j = in.ty0 + ty;
+                own = j >= y0 && j < y1;
+                out = ciede2000(srgb_to_lab(triangle_colour(s, m, P, (int)(key & 0xFFFFu), i, j)), gld(s.olab + e.y)) > s.tau;
+                if (nnm && !out) mark_nn<false>(bits, e.y, s.W, in.jx0, by0, in.jw, bh);
+            }
+            cR += wave_popc(out && own);
+        };
+        // marking from the n listed inliers, 64 at a time one per lane; with
+        // fewer chunks than waves, waves share a chunk's window rows
+        auto mark_list = [&](int n) {
+            const int chunks = (n + 63) >> 6, share = chunks > 0 ? max(NW / chunks, 1) : 1, teams = NW / share;
+            if (wave >= teams * share) return;
+            for (int c = wave / share; c < chunks; c += teams) {
+                const int nc = min(64, n - 64 * c);
+                const int kk = list[64 * c + min(lane, nc - 1)];
+                const uint32_t key = gld(tile + kk);
+                const int ty = window_row(kk, in.tw, tinv);
+                const int ei = in.tx0 + kk - ty * in.tw, ej = in.ty0 + ty, ed = (int)(key >> 16);
+                int X, Y, wuv;
+                mark_params(s, ei, ej, ed, &X, &Y, &wuv);
+                if (nc >= kLanesMin) {
+                    wave_mark_lanes<K>(ms, lane < nc, ei, ej, ed, kk, X, Y, wuv, mark_ellipse(s, ei, ej, ed),
+                                       (s.fx / s.fy) * (s.fx / s.fy), keys, in.jx0, by0, in.jw, bh, wave % share, share);
+                } else {
+                    for (int t = wave % share; t < nc; t += share)
+                        wave_mark<K>(ms, __builtin_amdgcn_readlane(ei, t), __builtin_amdgcn_readlane(ej, t),
+                                     __builtin_amdgcn_readlane(ed, t), __builtin_amdgcn_readlane(kk, t),
+                                     __builtin_amdgcn_readlane(X, t), __builtin_amdgcn_readlane(Y, t),
+                                     __builtin_amdgcn_readlane(wuv, t), keys, in.jx0, by0, in.jw, bh, lane);
+                }
+            }
+        };
+        int qc = 0;
+        auto push = [&](bool need, int a, int b, auto &&flush) {
+            const unsigned long long mq = __ballot(need);
+            if (need) q[qc + lane_rank(mq)] = make_int2(a, b);
+            qc += __popcll(mq);
+            if (qc >= 64) {
+                flush(64);
+                wave_lds_sync();
+                if (64 + lane < qc) q[lane] = q[64 + lane];     // the overflow moves to the front
+                qc -= 64;
+            }
+        };
+        // occluders, stride and J_r, a pixel per thread a turn; the list is
+        // marked from when it might not hold another turn's
+        const int ka = (ra - in.ty0) * in.tw, kb = (rb - in.ty0) * in.tw;
+        const bool marks = bpx > 0 && !nnm;
+        for (int k0 = ka; k0 < kb; k0 += kWideBlock) {
+            const int k = k0 + tid, kc = min(k, kb - 1);
+            const int ty = window_row(kc, in.tw, tinv), i = in.tx0 + kc - ty * in.tw, j = in.ty0 + ty;
+            const uint32_t pix = (uint32_t)(j * s.W + i), key = gld(tile + kc);
+            const int dob = mark ? (int)gld(s.depth + pix) : 0, d = (int)(key >> 16);
+            const int2 tr = knn2 || hsh ? make_int2(0, 0) : gld(s.thdr + pix);
+            bool keep = k < kb && key != kEmptyKey && (s.stride == 1 || (i % s.stride == 0 && j % s.stride == 0));
+            if (keep && dob > 0 && 16 * dob + s.dq < 16 * d
+                && (!(label_mode && s.labels) || s.labels[pix] != it.label))
+                keep = false;
+            int nn = -1;
+            if (knn2 || hsh) {
+                if (keep) {
+                    int X, Y, wuv;
+                    mark_params(s, i, j, d, &X, &Y, &wuv);
+                    nn = knn2 ? scan_nn(s, X, Y, 16 * d) : hash_nn(s, X, Y, 16 * d);
+                }
+            } else {
+                const int e = d - (tr.y & 0xFFFF);
+                const bool ok = keep && e >= 0 && e < (int)((uint32_t)tr.y >> 16);
+                nn = gld(s.tnn + (uint32_t)(ok ? tr.x + e : 0));
+                if (!ok) nn = -1;
+            }
+            const bool own = j >= y0 && j < y1, hit = nn >= 0;
+            cL += wave_popc(keep && own);
+            cR += wave_popc(keep && own && !hit);
+            if (nnm && !rgb && hit) mark_nn<false>(bits, nn, s.W, in.jx0, by0, in.jw, bh);
+            if (rgb) push(hit && (own || nnm), k, nn, flush_r);
+            if (marks) {
+                const unsigned long long mh = __ballot(hit);
+                int at = 0;
+                if (lane == 0 && mh) at = atomicAdd(&s_n, __popcll(mh));
+                at = __builtin_amdgcn_readfirstlane(at);
+                if (hit) list[at + lane_rank(mh)] = k;
+                __syncthreads();
+                const int n = __builtin_amdgcn_readfirstlane(s_n);
+                if (n > kWideList - kWideBlock || k0 + kWideBlock >= kb) {
+                    mark_list(n);
+                    __syncthreads();
+                    if (tid == 0) s_n = 0;
+                }
+                __syncthreads();
+            }
+        }
+        if (qc > 0) flush_r(qc);
+        qc = 0;
+        __syncthreads();
+        // J_o over the band's rows of the V region
+        const int va = max(y0, in.vy0), vb = min(y1, in.vy0 + in.vh);
+        const int rpx = max(vb - va, 0) * in.vw;
+        const float vinv = 1.0f / (float)max(in.vw, 1);
+        auto flush_o = [&](int n) {
+            wave_lds_sync();
+            bool cout = false;
+            if (lane < n) {
+                const int2 e = q[lane];
+                const uint32_t key = gld(tile + e.y);
+                const int ty = window_row(e.y, in.tw, tinv), tx = e.y - ty * in.tw;
+                const float4 lr = srgb_to_lab(triangle_colour(s, m, P, (int)(key & 0xFFFFu), in.tx0 + tx, in.ty0 + ty));
+                cout = ciede2000(gld(s.olab + e.x), lr) > s.tau;
+            }
+            cO += wave_popc(cout);
+        };
+        for (int k0 = wave * 64; k0 < rpx; k0 += 2 * kWideBlock) {
+            int ii[2], jj[2], pp[2];
+            int3 qq[2];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const int kc = min(k0 + u * kWideBlock + lane, rpx - 1);
+                const int vy = window_row(kc, in.vw, vinv);
+                ii[u] = in.vx0 + kc - vy * in.vw;
+                jj[u] = va + vy;
+                pp[u] = jj[u] * s.W + ii[u];
+                qq[u] = opt_at(ms.opt, (uint32_t)pp[u]);
+            }
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                if (k0 + u * kWideBlock >= rpx) break;
+                bool inq = k0 + u * kWideBlock + lane < rpx && qq[u].z != kNoPoint;
+                if (inq)
+                    inq = label_mode ? gld(s.labels + pp[u]) == it.label
+                                     : in_volume(m, P, qq[u].x, qq[u].y, qq[u].z >> 4, dl, cyl);
+                const int jx = ii[u] - in.jx0, jy = jj[u] - by0;
+                bool expl = false;
+                int kr = 0;
+                if (inq && jx >= 0 && jx < in.jw && jy >= 0 && jy < bh) {
+                    if (nnm) {
+                        expl = Marks<false>::test(bits, jy * in.jw + jx);
+                    } else {
+                        const unsigned long long key = keys[jy * in.jw + jx];
+                        expl = key != K::kEmpty;
+                        kr = K::index(key);
+                    }
+                }
+                cQ += wave_popc(inq);
+                cO += wave_popc(inq && !expl);
+                if (ocol) push(inq && expl, pp[u], kr, flush_o);
+            }
+        }
+        if (qc > 0) flush_o(qc);
+    }
+    if (lane == 0) {
+        atomicAdd(&cnt[0], cR);
+        atomicAdd(&cnt[1], cO);
+        atomicAdd(&cnt[2], cL);
+        atomicAdd(&cnt[3], cQ);
+    }
+    __syncthreads();
+    if (tid == 0) {
+        if (cnt[0]) atomicAdd(it.jr + in.local, cnt[0]);
+        if (cnt[1]) atomicAdd(it.jo + in.local, cnt[1]);
+        if (it.nr && cnt[2]) atomicAdd(it.nr + in.local, cnt[2]);
+        if (it.nq && cnt[3]) atomicAdd(it.nq + in.local, cnt[3]);
     }
 }
 
@@ -1436,6 +1749,21 @@ hipError_t launch_score_class(const Work &w, const LaunchCfg &c, int cls, bool a
     if (any_pv)
         return any_rgb ? launch_class_t<true, true>(w, c, cls, st) : launch_class_t<false, true>(w, c, cls, st);
     return any_rgb ? launch_class_t<true, false>(w, c, cls, st) : launch_class_t<false, false>(w, c, cls, st);
+}
+
+hipError_t launch_wide(const Work &w, int n_poses, int max_tris, int bands, bool any_rgb, bool any_pv, hipStream_t st)
+{
+    wide_setup_kernel<<<n_poses, 256, 0, st>>>(w);
+    wide_raster_kernel<<<dim3((max_tris + 255) / 256, n_poses), 256, 0, st>>>(w);
+    const dim3 g(bands, n_poses);
+    if (any_pv) {
+        if (any_rgb) wide_score_kernel<true, true><<<g, kWideBlock, 0, st>>>(w);
+        else wide_score_kernel<false, true><<<g, kWideBlock, 0, st>>>(w);
+    } else {
+        if (any_rgb) wide_score_kernel<true, false><<<g, kWideBlock, 0, st>>>(w);
+        else wide_score_kernel<false, false><<<g, kWideBlock, 0, st>>>(w);
+    }
+    return hipGetLastError();
 }
 
 hipError_t launch_item_argmin(const Work &w, int items_grid, hipStream_t st)

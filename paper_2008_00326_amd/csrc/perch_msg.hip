@@ -400,7 +400,7 @@ __global__ __launch_bounds__(BLOCK) void msg_kernel(MsgArgs a)
             // J_o over the observed points of V(O) outside every placed volume
             const int rpx = rw * rh;
             int co = 0, cq = 0;
-            const float dlw = s.delta + 0.25f, idlw = 1.0f / dlw;
+            const float dlw = s.delta + 0.25f;
             auto flush_o = [&](int n) {
                 wave_lds_sync();
                 bool out = false;
@@ -435,51 +435,17 @@ __global__ __launch_bounds__(BLOCK) void msg_kernel(MsgArgs a)
                             }
                         }
                     };
-                    // first the 4x4 tile of the pixel itself, or the nearest one
-                    const int ic = min(max(i - tx0, 0), tw - 1) & ~3, jc = min(max(j - ty0, 0), th - 1) & ~3;
-                    if (tpx > 0 && fast && (rgb || bd2 > s.dq2)) scan(ic, jc);
                     // without the colour term any point within delta will do
                     if (tpx > 0 && (rgb || bd2 > s.dq2)) {
-                        // pixels that can hold a point at most the best's
-                        // distance away: the window of radius e in place of
-                        // delta + 1/4 (the factor covers the binary32 rounding)
-                        const float e = bd2 > s.dq2 ? dlw : fminf((float)((int)sqrtf((float)bd2) + 1) * 0.0625f + 0.25f, dlw);
-                        const float iz = window_inv(o.z >> 4, e), f = e * idlw * 1.000004f;
-                        const int wu = window_half(gld(s.ax + i) * f, iz, s.W), wv = window_half(gld(s.ay + j) * f, iz, s.H);
-                        const int i0 = max(i - wu, tx0), i1 = min(i + wu, tx0 + tw - 1);
-                        const int j0 = max(j - wv, ty0), j1 = min(j + wv, ty0 + th - 1);
-                        if (i0 <= i1 && j0 <= j1) {
-                            if (fast) {
-                                const int bx1 = (i1 - tx0) >> 2, by1 = (j1 - ty0) >> 2;
-                                // blocks of 8x8 tiles, one bit each
-                                for (int by = (j0 - ty0) >> 2; by <= by1; by += 8)
-                                    for (int bx = (i0 - tx0) >> 2; bx <= bx1; bx += 8) {
-                                        auto near_enough = [&](int b) {
-                                            const uint32_t r = range[(by + (b >> 3)) * bw + bx + (b & 7)];
-                                            const int dz = max(max(16 * (int)(r & 0xFFFFu) - o.z, o.z - 16 * (int)(r >> 16)), 0);
-                                            return dz <= s.dq && __mul24(dz, dz) <= bd2;
-                                        };
-                                        unsigned long long mask = 0;
-                                        for (int y = 0; y < 8 && by + y <= by1; ++y)
-                                            for (int x = 0; x < 8 && bx + x <= bx1; ++x)
-                                                if (near_enough(8 * y + x)) mask |= 1ULL << (8 * y + x);
-                                        const int bc = 8 * ((jc >> 2) - by) + (ic >> 2) - bx;     // scanned already
-                                        if ((jc >> 2) >= by && (jc >> 2) < by + 8 && (ic >> 2) >= bx && (ic >> 2) < bx + 8)
-                                            mask &= ~(1ULL << bc);
-                                        while (mask) {
-                                            const int b = __ffsll(mask) - 1;
-                                            mask &= mask - 1;
-                                            if (!near_enough(b)) continue;
-                                            scan(4 * (bx + (b & 7)), 4 * (by + (b >> 3)));
-                                            if (!rgb && bd2 <= s.dq2) mask = 0;
-                                        }
-                                    }
-                            } else {
-                                for (int jj = j0; jj <= j1; ++jj)
-                                    for (int ii = i0; ii <= i1; ++ii)
-                                        take(tkey((jj - ty0) * tw + (ii - tx0)), gld(s.kx + ii), gld(s.ky + jj),
-                                             jj * s.W + ii);
-                            }
+                        if (fast) {
+                            nearest_rendered(s, o, i, j, tx0, ty0, tw, th, !rgb, bd2, [&](int b) { return range[b]; },
+                                             [&](int b) { scan(4 * (b % bw), 4 * (b / bw)); });
+                        } else {
+                            const float iz = window_inv(o.z >> 4, dlw);
+                            const int wu = window_half(gld(s.ax + i), iz, s.W), wv = window_half(gld(s.ay + j), iz, s.H);
+                            for (int jj = max(j - wv, ty0); jj <= min(j + wv, ty0 + th - 1); ++jj)
+                                for (int ii = max(i - wu, tx0); ii <= min(i + wu, tx0 + tw - 1); ++ii)
+                                    take(tkey((jj - ty0) * tw + (ii - tx0)), gld(s.kx + ii), gld(s.ky + jj), jj * s.W + ii);
                         }
                     }
                     out = bd2 > s.dq2;

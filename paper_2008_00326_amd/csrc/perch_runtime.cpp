@@ -464,6 +464,18 @@ std::vector<int> label_box(SceneRec &r, int32_t label)
     return b;
 }
 
+// Launches of at most this many poses take the wide path.  Both ways over
+// (class kernels / wide, us a call): 640x480 RGB, 160 poses 595 / 296, 320
+// 630 / 364, 480 642 / 550, 640 670 / 750; 320x240 depth, 128 135 / 86, 400
+// 139 / 119, 512 140 / 138; nearest-neighbour marking, 512 327 / 406.
+constexpr int kWideMaxPoses = 384;
+// Work-groups its scoring aims at (two per compute unit are resident): more
+// bands shorten the longest one but redo more rows (320x240, 400 poses: 119
+// us at 1024, 134 at 2048; 640x480, 256 poses of near-truth candidates 323
+// and 263).
+constexpr int kWideGroups = 1024;
+constexpr int kWideMaxBands = 32;   // one pose: 114 us at 16, 80 at 32, 73 at 64
+
 size_t align64(size_t x) { return (x + 63) & ~(size_t)63; }
 
 // Host image of a launch's descriptors: header | items | scenes | meshes.
@@ -472,6 +484,7 @@ struct Built {
     size_t items_off = 64, scenes_off = 0, meshes_off = 0;
     int n_items = 0, n_poses = 0;
     size_t max_pixels = 0;
+    int max_tris = 0;
     bool any_rgb = false;
     bool any_pv = false;   // some scene takes one of the paper's variants (NN marking, kNN II)
     std::vector<int32_t> scene_ids, mesh_ids;
@@ -540,6 +553,7 @@ perch_status build_descriptors(perch_ctx *ctx, const perch_work *req, int32_t n_
         items.push_back(it);
         total += q.n_poses;
         b.max_pixels = std::max(b.max_pixels, (size_t)sd.W * sd.H);
+        b.max_tris = std::max(b.max_tris, mi->second.dev.nt);
         b.any_rgb |= (sd.flags & PERCH_USE_RGB) != 0;
         b.any_pv |= (sd.flags & (PERCH_JO_NN | PERCH_KNN2 | PERCH_HASH)) != 0;
         if (sd.flags & PERCH_KNN1)
@@ -652,6 +666,18 @@ hipError_t enqueue(perch_ctx *ctx, const Work &w, const LaunchCfg &cfg, int pose
     return e;
 }
 
+// The work-groups per pose of a launch's wide path, 0 for the class kernels.
+int wide_bands(const perch_ctx *ctx, const Built &b, const LaunchCfg &cfg)
+{
+    const perch_tuning &t = ctx->tune;
+    if (t.small_block || t.small_words || t.grid[0] || t.grid[1] || t.grid[2] || t.grid[3] || t.order || t.key_bands)
+        return 0;
+    size_t sw[kNumClasses], sb[kNumClasses], total = 0, tile = 0;
+    slot_layout(cfg, b.max_pixels, sw, sb, &total, &tile);
+    if (b.n_poses > kWideMaxPoses || (size_t)b.n_poses * tile > total) return 0;
+    return std::max(1, std::min(kWideGroups / b.n_poses, kWideMaxBands));
+}
+
 // Copy descriptors to the device through a pinned staging slot, asynchronously.
 perch_status upload(StreamBufs &sb, const void *src, size_t n, void *dev, hipStream_t st)
 {
@@ -698,7 +724,15 @@ perch_status run_direct(perch_ctx *ctx, const perch_work *req, int32_t n_req, hi
     if (perch_status s = upload(sb, b.bytes.data(), b.bytes.size(), sb.lb.desc.ptr, st)) return s;
     const Work w = make_work(sb.lb, b, b.n_poses, cfg, b.max_pixels, want_best);
     sb.last_n = b.n_poses;
-    hipError_t e = enqueue(ctx, w, cfg, b.n_poses, b.n_items, b.any_rgb, b.any_pv, st, true);
+    const int bands = rflag || oflag ? 0 : wide_bands(ctx, b, cfg);
+    hipError_t e = hipSuccess;
+    if (bands > 0) {
+        e = ctx->timed(kProfWide, st,
+                       [&] { return launch_wide(w, b.n_poses, b.max_tris, bands, b.any_rgb, b.any_pv, st); });
+        if (e == hipSuccess && w.best) e = ctx->timed(kProfArgmin, st, [&] { return launch_item_argmin(w, b.n_items, st); });
+    } else {
+        e = enqueue(ctx, w, cfg, b.n_poses, b.n_items, b.any_rgb, b.any_pv, st, true);
+    }
     if (e != hipSuccess) return fail(PERCH_EDEVICE, "score launch: %s", hipGetErrorString(e));
     mark_uses(ctx, b.scene_ids, b.mesh_ids, st);
     return PERCH_OK;
@@ -2042,16 +2076,10 @@ perch_status perch_last_classes(perch_ctx *ctx, void *hip_stream, int32_t n, int
     if (it == ctx->work.end() || it->second.last_n <= 0) return fail(PERCH_ENOTFOUND, "no scoring call on this stream");
     StreamBufs &b = it->second;
     if (n != b.last_n || !class_host) return fail(PERCH_EINVAL, "n must equal the last call's %d poses", b.last_n);
-    std::vector<int32_t> counts(kNumClasses), lists((size_t)kNumClasses * n);
+    std::vector<PoseInfo> info((size_t)n);     // every launch classifies its poses, whichever kernels score them
     HIP_TRY(hipStreamSynchronize(st));
-    HIP_TRY(hipMemcpy(counts.data(), b.lb.counts.ptr, kNumClasses * 4, hipMemcpyDeviceToHost));
-    HIP_TRY(hipMemcpy(lists.data(), b.lb.lists.ptr, lists.size() * 4, hipMemcpyDeviceToHost));
-    for (int32_t i = 0; i < n; ++i) class_host[i] = -1;
-    for (int c = 0; c < kNumClasses; ++c)
-        for (int32_t k = 0; k < counts[c] && k < n; ++k) {
-            const int32_t p = lists[(size_t)c * n + k];
-            if (p >= 0 && p < n) class_host[p] = c;
-        }
+    HIP_TRY(hipMemcpy(info.data(), b.lb.info.ptr, info.size() * sizeof(PoseInfo), hipMemcpyDeviceToHost));
+    for (int32_t i = 0; i < n; ++i) class_host[i] = info[i].order / (kNumStrips * kNumBuckets);
     return ok();
 }
 
