@@ -232,17 +232,25 @@ __device__ void wave_mark(const MarkScene &s, int i, int j, int d, int k, int X,
     }
 }
 
-// Wave-wide minimum and maximum of a lane value.
+// Wave-wide minimum and maximum of a lane value, wave-uniform (every lane
+// active): DPP steps within rows of 16 and across them into lane 63, a short
+// chain where shuffles through LDS would each take its latency.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int dpp_from(int v)
+{
+    return __builtin_amdgcn_update_dpp(v, v, CTRL, ROWS, 0xF, false);   // lanes without a source keep their own
+}
 __device__ __forceinline__ int wave_min(int v)
 {
-    for (int o = 32; o > 0; o >>= 1) v = min(v, __shfl_xor(v, o));
-    return v;
+    v = min(v, dpp_from<0x111, 0xF>(v));     // row_shr 1, 2, 4, 8
+    v = min(v, dpp_from<0x112, 0xF>(v));
+    v = min(v, dpp_from<0x114, 0xF>(v));
+    v = min(v, dpp_from<0x118, 0xF>(v));
+    v = min(v, dpp_from<0x142, 0xA>(v));     // row_bcast 15, 31
+    v = min(v, dpp_from<0x143, 0xC>(v));
+    return __builtin_amdgcn_readlane(v, 63);
 }
-__device__ __forceinline__ int wave_max(int v)
-{
-    for (int o = 32; o > 0; o >>= 1) v = max(v, __shfl_xor(v, o));
-    return v;
-}
+__device__ __forceinline__ int wave_max(int v) { return ~wave_min(~v); }
 
 // Inliers a wave marks together, one per lane, at least: below it each
 // inlier takes the whole wave (wave_mark), since the lanes' shared offset
@@ -269,13 +277,13 @@ __device__ void wave_mark_lanes(const MarkScene &s, bool act, int i, int j, int 
     int x0 = max(max(-wu, -i), jx0 - i), x1 = min(min(wu, s.W - 1 - i), jx0 + jw - 1 - i);
     int y0 = max(max(-wv, -j), jy0 - j), y1 = min(min(wv, s.H - 1 - j), jy0 + jh - 1 - j);
     const bool live = act && x0 <= x1 && y0 <= y1;
-    const int DX0 = __builtin_amdgcn_readfirstlane(wave_min(live ? x0 : 1 << 20));
-    const int DX1 = __builtin_amdgcn_readfirstlane(wave_max(live ? x1 : -(1 << 20)));
-    const int DY0 = __builtin_amdgcn_readfirstlane(wave_min(live ? y0 : 1 << 20));
-    const int DY1 = __builtin_amdgcn_readfirstlane(wave_max(live ? y1 : -(1 << 20)));
+    const int DX0 = wave_min(live ? x0 : 1 << 20);
+    const int DX1 = wave_max(live ? x1 : -(1 << 20));
+    const int DY0 = wave_min(live ? y0 : 1 << 20);
+    const int DY1 = wave_max(live ? y1 : -(1 << 20));
     if (DX0 > DX1) return;
     // non-negative binary32 values order as their bit patterns
-    const float Em = __int_as_float(__builtin_amdgcn_readfirstlane(wave_max(live ? __float_as_int(E) : 0)));
+    const float Em = __int_as_float(wave_max(live ? __float_as_int(E) : 0));
     if (!live) x0 = x1 = y0 = y1 = 0;                 // idle lanes re-read their own pixel
     const int Z = 16 * d;
     const int dq2 = s.dq2;
@@ -745,6 +753,315 @@ __device__ __forceinline__ void score_pose(const Work &w, int p, uint32_t *tile,
     __syncthreads();
 }
 
+
+// Work lists of a work-group in LDS: a turn of the scans below puts at most
+// 4 BLOCK entries into a list of 8 BLOCK, and the list is worked off when
+// another turn might overflow it.
+template <int BLOCK> constexpr int kListCap = 8 * BLOCK;
+
+// One pose of the LDS classes (tile and J_o keys in LDS) in launches without
+// the paper's variants (whose poses, with no marking to share out, take longer
+// with the list's barriers: 1,200 nearest-neighbour poses an object, 1.20 ms
+// against 1.12).  The inliers of the
+// whole group go into one list and their colour tests and marking are shared
+// out over its waves: full waves of 64 tests whatever the spread of the
+// inliers over the image, and every wave marking (in units of some window
+// rows of 64 inliers) until the last unit is done.  With a queue per wave a
+// flush carried 29 inliers on average, and the waves over the object's near
+// side marked while the others waited at the barrier: 32,000 poses of one
+// object with colour 13.66 -> 11.86 ms, 8,000 6-DoF poses without 6.27 ->
+// 5.99, 512 poses of a grid without 121 -> 113 us.  What bounds it now is
+// vector work and LDS atomics of the marking (28-40 us of a large pose's
+// ~100), then the raster (9-15, 6-DoF 44-65) and the two window scans (16-20
+// each).
+template <int BLOCK, bool RGB>
+__device__ __forceinline__ void score_pose_lds(const Work &w, int p, uint32_t *tile, uint32_t *keys, float4 *labs,
+                                               int *cnt, uint16_t *list, int *s_n)
+{
+    constexpr int NW = BLOCK / 64;
+    using K = KeyOf<false>;
+    const int tid = threadIdx.x;
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const PoseInfo in = w.info[p];
+    const ItemDev &it = w.items[in.item];
+    const SceneDev &s = w.scenes[it.scene];
+    const MeshDev &m = w.meshes[it.mesh];
+    const bool rgb = RGB && (s.flags & 1u) != 0;
+    float P[12];
+#pragma unroll
+    for (int k = 0; k < 12; ++k) P[k] = it.poses[12 * (size_t)in.local + k];
+    // what heads a loop with barriers is wave-uniform by construction (readfirstlane)
+    const int tpx = __builtin_amdgcn_readfirstlane(in.tw * in.th);
+    const int jpx = in.jw * in.jh;
+    const float tinv = 1.0f / (float)max(in.tw, 1);
+    const MarkScene ms = mark_scene(s);
+    // class images of the inspection entry point: rendered pixels 1 inlier,
+    // 2 no neighbour, 3 colour mismatch, 4 occluded; observed pixels of V(O)
+    // 1 explained, 2 no neighbour, 3 colour mismatch
+    uint8_t *const rf = it.rflag ? it.rflag + (size_t)in.local * s.W * s.H : nullptr;
+    uint8_t *const of = it.oflag ? it.oflag + (size_t)in.local * s.W * s.H : nullptr;
+    const bool mark = (s.flags & 2u) != 0;
+    const bool label_mode = (s.flags & (3u << 4)) == (2u << 4);
+    const bool cyl = (s.flags & (3u << 4)) == (1u << 4);
+
+    for (int k = tid; k < tpx; k += BLOCK) tile[k] = kEmptyKey;
+    if (tid < 4) cnt[tid] = 0;
+    if (tid == 4) *s_n = 0;
+    // 0. with LDS to spare beyond the tile (the J_o keys are cleared only
+    //    after the raster), every vertex is projected once for the pose
+    const int tile_q = (tpx + 3) & ~3;
+    const int4 *vcache = nullptr;
+    if (tpx > 0 && 4 * m.nv <= (BLOCK == 1024 ? w.cap_large : w.cap_small) - tile_q) {
+        int4 *vc = reinterpret_cast<int4 *>(tile + tile_q);
+        for (int v = tid; v < m.nv; v += BLOCK) vc[v] = pack_vtx(project_vertex(P, gld(m.verts + v), s));
+        vcache = vc;
+    }
+    __syncthreads();
+
+    // 1. raster
+    if (tpx > 0) {
+        for (int t0 = 0; t0 < m.nt; t0 += BLOCK) {
+            const int t = t0 + tid;
+            if (t < m.nt) raster_triangle<false>(s, m, P, t, in.tx0, in.ty0, in.tw, in.th, tile, vcache);
+        }
+    }
+    __syncthreads();
+
+    // J_o keys held at once: the whole J_o region, or, for a pose of the
+    // 1024-thread class whose region does not fit beside its tile, bands of
+    // rows; phases 2 and 3 then run once per band, every inlier marking the
+    // band's keys, and the J_r counts are taken in the first band.
+    int hb = in.jh;
+    if (BLOCK == 1024 && in.jw > 0 && tpx + jpx > w.cap_large) hb = (w.cap_large - tpx) / in.jw;
+    hb = __builtin_amdgcn_readfirstlane(hb);
+    const int nb = __builtin_amdgcn_readfirstlane(in.jh > 0 ? (in.jh + hb - 1) / hb : 1);
+    int cL = 0, cR = 0, cQ = 0, cO = 0;
+    const double dl = (double)s.delta;
+    // appends the lanes' entries (bit u of a lane's `need`, value v0 + u step) to the list
+    auto push = [&](const unsigned long long hit[4], int v0, int step) {
+        int total = 0;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) total += __popcll(hit[u]);
+        if (total == 0) return;
+        int at = 0;
+        if (lane == 0) at = atomicAdd(s_n, total);
+        at = __builtin_amdgcn_readfirstlane(at);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            if (hit[u] >> lane & 1) list[at + lane_rank(hit[u])] = (uint16_t)(v0 + u * step);
+            at += __popcll(hit[u]);
+        }
+    };
+    // after a turn: works the list off when the next turn might overflow it,
+    // and after the last one.  `held` bounds its length without a barrier.
+    auto turn = [&](int &held, bool last, auto &&work) {
+        held += 4 * BLOCK;
+        if (!last && held + 4 * BLOCK <= kListCap<BLOCK>) return;
+        __syncthreads();
+        held = __builtin_amdgcn_readfirstlane(*s_n);
+        if (last || held + 4 * BLOCK > kListCap<BLOCK>) {
+            work(held);
+            held = 0;
+            __syncthreads();
+            if (tid == 0) *s_n = 0;
+        }
+        __syncthreads();
+    };
+    for (int b = 0; b < nb; ++b) {
+        const bool first = b == 0;
+        const int by0 = in.jy0 + b * hb;
+        const int bh = in.jh > 0 ? min(hb, in.jy0 + in.jh - by0) : 0;
+        const int bpx = in.jw * bh;
+        for (int k = tid; k < bpx; k += BLOCK) keys[k] = K::kEmpty;
+
+        // 2. first band: occluders (Eq. 3) and the downsampling stride; J_r:
+        //    nearest observed neighbour from the scene table.  Listed inliers
+        //    are colour-tested (Eq. 4, first band) and mark the observed
+        //    points they explain.
+        auto inlier = [&](int e, int &kk, uint32_t &key, int &i, int &j) {
+            kk = list[e];
+            key = tile[kk];
+            const int ty = tile_row<false>(kk, in.tw, tinv);
+            i = in.tx0 + kk - __mul24(ty, in.tw);
+            j = in.ty0 + ty;
+        };
+        auto table_nn = [&](int2 th, int d) {
+            const int e = d - (th.y & 0xFFFF);
+            const bool ok = e >= 0 && e < (int)((uint32_t)th.y >> 16);
+            const int t = gld(s.tnn + (uint32_t)(ok ? th.x + e : 0));
+            return ok ? t : -1;
+        };
+        auto work_r = [&](int n) {
+            if (rgb && first)
+                for (int e0 = 64 * wave; e0 < n; e0 += BLOCK) {
+                    bool out = false;
+                    if (e0 + lane < n) {
+                        int kk, i, j;
+                        uint32_t key;
+                        inlier(e0 + lane, kk, key, i, j);
+                        const int nn = max(table_nn(gld(s.thdr + (uint32_t)(j * s.W + i)), (int)(key >> 16)), 0);
+                        const float4 lr = srgb_to_lab(triangle_colour(s, m, P, (int)(key & 0xFFFFu), i, j));
+                        if (labs) labs[kk] = lr;     // kept for the J_o test of the points this inlier keys
+                        out = ciede2000(lr, gld(s.olab + nn)) > s.tau;
+                        if (rf) rf[j * s.W + i] = out ? 3 : 1;
+                    }
+                    cR += wave_popc(out);
+                }
+            if (bpx == 0 || n == 0) return;
+            const int chunks = (n + 63) >> 6, parts = max(1, min(8, 2 * NW / chunks));
+            for (int u = wave; u < chunks * parts; u += NW) {
+                const int c = u / parts, part = u - c * parts, nc = min(64, n - 64 * c);
+                int kk, i, j, X, Y, wuv;
+                uint32_t key;
+                inlier(64 * c + min(lane, nc - 1), kk, key, i, j);
+                const int d = (int)(key >> 16);
+                mark_params(s, i, j, d, &X, &Y, &wuv);
+                if (nc >= kLanesMin) {
+                    wave_mark_lanes<K>(ms, lane < nc, i, j, d, kk, X, Y, wuv, mark_ellipse(s, i, j, d),
+                                       (s.fx / s.fy) * (s.fx / s.fy), keys, in.jx0, by0, in.jw, bh, part, parts);
+                } else {
+                    for (int t = part; t < nc; t += parts)
+                        wave_mark<K>(ms, __builtin_amdgcn_readlane(i, t), __builtin_amdgcn_readlane(j, t),
+                                     __builtin_amdgcn_readlane(d, t), __builtin_amdgcn_readlane(kk, t),
+                                     __builtin_amdgcn_readlane(X, t), __builtin_amdgcn_readlane(Y, t),
+                                     __builtin_amdgcn_readlane(wuv, t), keys, in.jx0, by0, in.jw, bh, lane);
+                }
+            }
+        };
+        int held = 0;
+        // four chunks a turn: every chunk's depths and table entries are
+        // loaded (every lane loads, at a clamped pixel) before any is tested
+        for (int k0 = wave * 64; k0 - wave * 64 < tpx; k0 += 4 * BLOCK) {
+            uint32_t key[4];
+            int pp[4], dob[4], nn[4];
+            int2 th[4];
+            bool keep[4];
+            unsigned long long hit[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int k = k0 + u * BLOCK + lane, kc = min(k, tpx - 1);
+                key[u] = k < tpx ? tile[kc] : kEmptyKey;
+                const int ty = tile_row<false>(kc, in.tw, tinv), tx = kc - __mul24(ty, in.tw);
+                pp[u] = (in.ty0 + ty) * s.W + in.tx0 + tx;
+                dob[u] = mark && first ? (int)gld(s.depth + (uint32_t)pp[u]) : 0;
+                th[u] = gld(s.thdr + (uint32_t)pp[u]);
+                keep[u] = key[u] != kEmptyKey;
+                if (first && s.stride != 1) keep[u] = keep[u] && (in.tx0 + tx) % s.stride == 0 && (in.ty0 + ty) % s.stride == 0;
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) nn[u] = table_nn(th[u], (int)(key[u] >> 16));
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int k = k0 + u * BLOCK + lane, d = (int)(key[u] >> 16);
+                if (first) {
+                    if (keep[u] && dob[u] > 0 && 16 * dob[u] + s.dq < 16 * d
+                        && (!(label_mode && s.labels) || s.labels[pp[u]] != it.label)) {
+                        keep[u] = false;
+                        if (rf) rf[pp[u]] = 4;
+                    }
+                    if (key[u] != kEmptyKey && !keep[u]) tile[k] = kEmptyKey;
+                    cL += wave_popc(keep[u]);
+                }
+                const bool in_reach = keep[u] && nn[u] >= 0;
+                if (first) {
+                    cR += wave_popc(keep[u] && !in_reach);
+                    if (rf && keep[u] && (!in_reach || !rgb)) rf[pp[u]] = in_reach ? 1 : 2;
+                }
+                hit[u] = __ballot(in_reach && ((rgb && first) || bpx > 0));
+            }
+            push(hit, k0 + lane, BLOCK);
+            turn(held, k0 - wave * 64 + 4 * BLOCK >= tpx, work_r);
+        }
+        if (tpx == 0) __syncthreads();
+
+        // 3. J_o: observed points in V(O); explained iff some rendered point
+        //    keyed it.  In RGB mode the key names the nearest rendered point,
+        //    and the explained points are listed and colour-tested.  V rows
+        //    above the J_o region go with the first band, rows below it with
+        //    the last; pieces of at most 2^16 pixels, a list entry's range.
+        const int ra = __builtin_amdgcn_readfirstlane(first ? in.vy0 : by0);
+        const int rb = __builtin_amdgcn_readfirstlane(in.vw > 0 ? (b == nb - 1 ? in.vy0 + in.vh : by0 + bh) : ra);
+        const int piece = __builtin_amdgcn_readfirstlane(max(65536 / max(in.vw, 1), 1));
+        const float vinv = 1.0f / (float)max(in.vw, 1);
+        for (int r0 = ra; r0 < rb; r0 += piece) {
+            const int rpx = __builtin_amdgcn_readfirstlane(min(piece, rb - r0) * in.vw);
+            auto vpixel = [&](int k, int &i, int &j) {
+                const int vy = window_row(k, in.vw, vinv), vx = k - vy * in.vw;
+                i = in.vx0 + vx;
+                j = r0 + vy;
+                return j * s.W + i;
+            };
+            auto work_o = [&](int n) {
+                for (int e0 = 64 * wave; e0 < n; e0 += BLOCK) {
+                    bool cout = false;
+                    if (e0 + lane < n) {
+                        int i, j;
+                        const int pix = vpixel(list[e0 + lane], i, j);
+                        const int kr = K::index(keys[(j - by0) * in.jw + i - in.jx0]);
+                        float4 lr;
+                        if (labs) {
+                            lr = gld(labs + kr);       // every keying point is an inlier of the first band
+                        } else {
+                            const uint32_t key = tile[kr];
+                            const int ty = tile_row<false>(kr, in.tw, tinv), tx = kr - __mul24(ty, in.tw);
+                            lr = srgb_to_lab(triangle_colour(s, m, P, (int)(key & 0xFFFFu), in.tx0 + tx, in.ty0 + ty));
+                        }
+                        cout = ciede2000(gld(s.olab + pix), lr) > s.tau;
+                        if (of) of[pix] = cout ? 3 : 1;
+                    }
+                    cO += wave_popc(cout);
+                }
+            };
+            held = 0;
+            // four chunks a turn, every point loaded before any is tested
+            for (int k0 = wave * 64; k0 - wave * 64 < rpx; k0 += 4 * BLOCK) {
+                int ii[4], jj[4], pp[4];
+                int3 qq[4];
+                unsigned long long hit[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) pp[u] = vpixel(min(k0 + u * BLOCK + lane, rpx - 1), ii[u], jj[u]);
+#pragma unroll
+                for (int u = 0; u < 4; ++u) qq[u] = opt_at(ms.opt, (uint32_t)pp[u]);
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    bool inq = k0 + u * BLOCK + lane < rpx && qq[u].z != kNoPoint;
+                    if (inq)
+                        inq = label_mode ? gld(s.labels + pp[u]) == it.label
+                                         : in_volume(m, P, qq[u].x, qq[u].y, qq[u].z >> 4, dl, cyl);
+                    bool expl = false;
+                    const int jx = ii[u] - in.jx0, jy = jj[u] - by0;
+                    if (inq && jx >= 0 && jx < in.jw && jy >= 0 && jy < bh)
+                        expl = keys[jy * in.jw + jx] != K::kEmpty;
+                    if (of && inq && (!expl || !rgb)) of[pp[u]] = expl ? 1 : 2;
+                    cQ += wave_popc(inq);
+                    cO += wave_popc(inq && !expl);
+                    hit[u] = __ballot(rgb && inq && expl);
+                }
+                if (rgb) {
+                    push(hit, k0 + lane, BLOCK);
+                    turn(held, k0 - wave * 64 + 4 * BLOCK >= rpx, work_o);
+                }
+            }
+        }
+        if (nb > 1) __syncthreads();      // the band's keys have been read
+    }
+
+    if (lane == 0) {
+        atomicAdd(&cnt[0], cR);
+        atomicAdd(&cnt[1], cO);
+        atomicAdd(&cnt[2], cL);
+        atomicAdd(&cnt[3], cQ);
+    }
+    __syncthreads();
+    if (tid == 0) {
+        it.jr[in.local] = cnt[0];
+        it.jo[in.local] = cnt[1];
+        if (it.nr) it.nr[in.local] = cnt[2];
+        if (it.nq) it.nq[in.local] = cnt[3];
+    }
+    __syncthreads();
+}
+
 // Persistent scoring kernel for one size class.  G: the tile lives in
 // device memory instead of LDS; KG: the J_o keys live in device memory
 // (64-bit) instead of LDS (32-bit, after the tile).  RGB: the colour term is
@@ -756,8 +1073,10 @@ __global__ __launch_bounds__(BLOCK, 4) void score_kernel(Work w, int cls)
 {
     extern __shared__ uint32_t smem[];
     __shared__ int cnt[4];
-    __shared__ int2 wq[BLOCK / 64 * 128];   // per-wave work queues of phases 3 and 4
-    __shared__ int next;
+    constexpr bool LDS = !G && !KG && !PV;
+    // work lists: the LDS classes' one for the group (16 bits an entry), else a queue per wave
+    __shared__ int2 wq[LDS ? kListCap<BLOCK> / 4 : BLOCK / 64 * 128];
+    __shared__ int next, s_n;
     uint32_t *slot = w.gscratch + w.slot_base[cls] + (size_t)blockIdx.x * w.slot_words[cls];
     float4 *labs = RGB && w.lab ? w.lab + w.lab_base[cls] + (size_t)blockIdx.x * w.lab_px[cls] : nullptr;
     // Ordered lists are cut into image strips, one per XCD: a work-group
@@ -793,7 +1112,8 @@ __global__ __launch_bounds__(BLOCK, 4) void score_kernel(Work w, int cls)
                 keys = reinterpret_cast<unsigned long long *>(G ? slot + w.dev_tile_words : slot);
             else
                 keys = smem + w.info[p].tw * w.info[p].th;
-            score_pose<BLOCK, G, KG, RGB, PV>(w, p, tile, keys, labs, cnt, wq);
+            if constexpr (LDS) score_pose_lds<BLOCK, RGB>(w, p, tile, keys, labs, cnt, reinterpret_cast<uint16_t *>(wq), &s_n);
+            else score_pose<BLOCK, G, KG, RGB, PV>(w, p, tile, keys, labs, cnt, wq);
             if (threadIdx.x == 0) next = atomicAdd(&w.counts[kCntNext + seg], 1);
             __syncthreads();
             i = __builtin_amdgcn_readfirstlane(next);

@@ -108,3 +108,25 @@ def test_footprints_beyond_the_lds(ctx):
     ctx.unload_mesh(mid)
     assert np.array_equal(a, b)
     assert a[2].max() > 40960 and a[0].min() < a[2].max() // 10
+
+
+@pytest.mark.parametrize("h,z,delta", [(80, 520, 10.0), (39, 250, 15.5), (35, 250, 15.5), (80, 900, 10.0)])
+def test_lists_of_many_inliers(ctx, h, z, delta):
+    """Every rendered point an inlier: the class kernels' work lists fill and
+    are worked off several times, and near the camera the observed window
+    is longer than a list entry's range."""
+    K = (640, 480, 500.0, 510.0, 320.0, 240.0)
+    cube = box((-h, -h, -h), (h, h, h), n=6, rgb_seed=11)
+    P0 = pose_matrix(rot_x(0.2), (5, -4, z))
+    d, _, c = oracle.render(cube, P0, K)
+    say(f"lists: cube of {2 * h} mm at {z} mm, delta {delta}")
+    for use_rgb in (True, False):
+        sid = ctx.set_scene(K, d, c, delta_mm=delta, tau_c=10.0, use_rgb=use_rgb)
+        mid = ctx.load_mesh(cube.xyz, cube.tri, cube.rgb)
+        poses = np.stack([P0, pose_matrix(rot_x(0.2), (8, -3, z + 4)), pose_matrix(rot_x(0.25), (2, -6, z - 1))])
+        a, b = both(ctx, sid, mid, poses)
+        classes = ctx.last_classes(len(poses))
+        ctx.drop_scene(sid)
+        ctx.unload_mesh(mid)
+        assert np.array_equal(a, b)
+        assert a[2].max() > 4096 and (classes <= 1).any()
