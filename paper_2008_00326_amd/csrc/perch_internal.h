@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <vector>
 
 namespace perch {
 
@@ -130,7 +131,11 @@ hipError_t launch_table_ranges(const SceneDev &s, uint32_t *tmp, int2 *thdr, lon
 int table_scan_blocks(int n_pixels);
 // Fills the table; entries at or past `cap` are not written (a table sized
 // on the host holds exactly the count the ranges kernels reach).
-hipError_t launch_table_fill(const SceneDev &s, int32_t *tnn, long long cap, hipStream_t st);
+// Window offsets of the table fill: {dx, dy in 16 bits each, the whole pixels of their distance in column units}.
+constexpr int kFillOffsMax = 16384;      // 128 KB
+void table_fill_offsets(const SceneDev &s, std::vector<int2> *out, int *bits);
+hipError_t launch_table_fill(const SceneDev &s, const int2 *offs, int n_offs, int bits, int32_t *tnn, long long cap,
+                             hipStream_t st);
 constexpr uint32_t kHashFlag = 1u << 9;   // PERCH_HASH
 // Uniform-grid voxel hash of the observed cloud: count points per bucket,
 // exclusive scan into s.hstart (2^hbits + 1 ints), scatter into s.hpts.

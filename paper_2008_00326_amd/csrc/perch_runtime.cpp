@@ -111,7 +111,7 @@ struct MeshRec {
 };
 
 struct SceneRec {
-    DevBuf depth, rgb, labels, opt, olab, kx, ky, ax, ay, thdr, tnn, hstart, hpts;
+    DevBuf depth, rgb, labels, opt, olab, axes, thdr, tnn, hstart, hpts;   // axes: kx, ky, ax, ay, window offsets
     SceneDev dev{};
     long long table_entries = 0;        // entries of the nearest-neighbour table (0 with the voxel hash)
     bool table_on_host = false;         // its size counted on the host (a batch was running)
@@ -808,7 +808,7 @@ perch_status perch_destroy(perch_ctx *ctx)
     for (auto &kv : ctx->scenes) {
         SceneRec &r = kv.second;
         FenceRef f = ctx->fence_of(r.uses);
-        for (DevBuf *b : {&r.depth, &r.rgb, &r.labels, &r.opt, &r.olab, &r.kx, &r.ky, &r.ax, &r.ay, &r.thdr,
+        for (DevBuf *b : {&r.depth, &r.rgb, &r.labels, &r.opt, &r.olab, &r.axes, &r.thdr,
                           &r.tnn, &r.hstart, &r.hpts})
             ctx->release(*b, f);
     }
@@ -1063,7 +1063,7 @@ perch_status perch_set_scene(perch_ctx *ctx, const perch_scene_desc *d, int32_t 
     auto up8 = [](size_t x) { return (x + 7) & ~(size_t)7; };
     const size_t o_depth = 0, o_rgb = up8(N * 2), o_lab = o_rgb + (use_rgb ? up8(N * 3) : 0);
     const size_t o_kx = o_lab + (d->labels ? up8(N * 4) : 0), o_ky = o_kx + (size_t)W * 8, o_ax = o_ky + (size_t)H * 8;
-    const size_t o_ay = o_ax + up8((size_t)W * 4), o_total = o_ay + up8((size_t)H * 4), stage_bytes = o_total + 8;
+    const size_t o_ay = o_ax + up8((size_t)W * 4), o_offs = o_ay + up8((size_t)H * 4);
     // Window half-sizes that hold every neighbour pair of this scene: a
     // rendered point with an observed neighbour has depth >= dmin - dzmm,
     // and the pixel window shrinks with depth.
@@ -1082,6 +1082,28 @@ perch_status perch_set_scene(perch_ctx *ctx, const perch_scene_desc *d, int32_t 
             wty = std::min(H, (int)(K.fy * dl * std::sqrt(1.0 + ry * ry) / (z - dl)) + 2);
         }
     }
+    SceneDev &s = r.dev;
+    s.hshift = hshift;
+    s.hbits = hbits;
+    s.W = W;
+    s.H = H;
+    s.fx = K.fx;
+    s.fy = K.fy;
+    s.cx = K.cx;
+    s.cy = K.cy;
+    s.dq = dq;
+    s.dq2 = s.dq * s.dq;
+    s.dzmm = dzmm;
+    s.delta = d->delta_mm;
+    s.tau = d->tau_c;
+    s.flags = d->flags;
+    s.stride = d->stride;
+    s.wtx = wtx;
+    s.wty = wty;
+    std::vector<int2> offs;
+    int rank_bits = 0;
+    if (!hashed) table_fill_offsets(s, &offs, &rank_bits);
+    const size_t o_total = o_offs + offs.size() * sizeof(int2), stage_bytes = o_total + 8;
     // The table's size decides its allocation.  While this context's batches
     // keep the device busy, waiting for the ranges kernels' count would wait
     // behind them (a scoring launch holds every compute unit): the host
@@ -1102,7 +1124,7 @@ perch_status perch_set_scene(perch_ctx *ctx, const perch_scene_desc *d, int32_t 
     // is not held up
     auto cleanup = [&]() {
         std::lock_guard<std::recursive_mutex> lk(ctx->mu);
-        for (DevBuf *b : {&r.depth, &r.rgb, &r.labels, &r.opt, &r.olab, &r.kx, &r.ky, &r.ax, &r.ay, &r.thdr,
+        for (DevBuf *b : {&r.depth, &r.rgb, &r.labels, &r.opt, &r.olab, &r.axes, &r.thdr,
                           &r.tnn, &r.hstart, &r.hpts, &tmp})
             ctx->release(*b);
         if (stg) ctx->scene_stage.push_back(stg);
@@ -1115,10 +1137,7 @@ perch_status perch_set_scene(perch_ctx *ctx, const perch_scene_desc *d, int32_t 
         };
         A(r.depth, N * 2);
         A(r.opt, N * sizeof(int4));
-        A(r.kx, W * 8);
-        A(r.ky, H * 8);
-        A(r.ax, W * 4);
-        A(r.ay, H * 4);
+        A(r.axes, o_total - o_kx);
         if (use_rgb) {
             A(r.rgb, N * 3);
             A(r.olab, N * sizeof(float4));
@@ -1166,35 +1185,20 @@ perch_status perch_set_scene(perch_ctx *ctx, const perch_scene_desc *d, int32_t 
     std::memcpy(hs + o_ky, ky.data(), H * 8);
     std::memcpy(hs + o_ax, ax.data(), W * 4);
     std::memcpy(hs + o_ay, ay.data(), H * 4);
-    SceneDev &s = r.dev;
+    if (!offs.empty()) std::memcpy(hs + o_offs, offs.data(), offs.size() * sizeof(int2));
     s.depth = (const uint16_t *)r.depth.ptr;
     s.opt = (const int4 *)r.opt.ptr;
     s.olab = (const float4 *)r.olab.ptr;
     s.labels = (const int32_t *)r.labels.ptr;
-    s.kx = (const double *)r.kx.ptr;
-    s.ky = (const double *)r.ky.ptr;
-    s.ax = (const float *)r.ax.ptr;
-    s.ay = (const float *)r.ay.ptr;
+    const char *axes = (const char *)r.axes.ptr - o_kx;
+    s.kx = (const double *)(axes + o_kx);
+    s.ky = (const double *)(axes + o_ky);
+    s.ax = (const float *)(axes + o_ax);
+    s.ay = (const float *)(axes + o_ay);
+    const int2 *offs_dev = (const int2 *)(axes + o_offs);
     s.thdr = (const int2 *)r.thdr.ptr;
     s.hstart = (const int *)r.hstart.ptr;
     s.hpts = (const int4 *)r.hpts.ptr;
-    s.hshift = hshift;
-    s.hbits = hbits;
-    s.W = W;
-    s.H = H;
-    s.fx = K.fx;
-    s.fy = K.fy;
-    s.cx = K.cx;
-    s.cy = K.cy;
-    s.dq = dq;
-    s.dq2 = s.dq * s.dq;
-    s.dzmm = dzmm;
-    s.delta = d->delta_mm;
-    s.tau = d->tau_c;
-    s.flags = d->flags;
-    s.stride = d->stride;
-    s.wtx = wtx;
-    s.wty = wty;
     // uploads from the pinned area, then points, colours and the search structure, all on the context stream
     long long *total_dev = (long long *)((char *)tmp.ptr + tmp_main);
     long long *blk_dev = (long long *)((char *)tmp.ptr + tmp_main + 64);
@@ -1207,10 +1211,7 @@ perch_status perch_set_scene(perch_ctx *ctx, const perch_scene_desc *d, int32_t 
         H2D(r.depth, o_depth, N * 2);
         if (use_rgb) H2D(r.rgb, o_rgb, N * 3);
         if (d->labels) H2D(r.labels, o_lab, N * 4);
-        H2D(r.kx, o_kx, W * 8);
-        H2D(r.ky, o_ky, H * 8);
-        H2D(r.ax, o_ax, W * 4);
-        H2D(r.ay, o_ay, H * 4);
+        H2D(r.axes, o_kx, o_total - o_kx);
         if (e == hipSuccess)
             e = ctx->timed(kProfScenePrep, cs, [&] {
                 hipError_t e2 = launch_scene_prep(s, (const uint8_t *)r.rgb.ptr, (int4 *)r.opt.ptr,
@@ -1226,7 +1227,7 @@ perch_status perch_set_scene(perch_ctx *ctx, const perch_scene_desc *d, int32_t 
             r.table_entries = host_total;
             r.table_on_host = true;
             e = ctx->timed(kProfScenePrep, cs,
-                           [&] { return launch_table_fill(s, (int32_t *)r.tnn.ptr, host_total, cs); });
+                           [&] { return launch_table_fill(s, offs_dev, (int)offs.size(), rank_bits, (int32_t *)r.tnn.ptr, host_total, cs); });
         }
     }
     if (!hashed && host_total < 0) {
@@ -1251,7 +1252,7 @@ perch_status perch_set_scene(perch_ctx *ctx, const perch_scene_desc *d, int32_t 
         }
         s.tnn = (const int32_t *)r.tnn.ptr;
         e = ctx->timed(kProfScenePrep, ctx->stream,
-                       [&] { return launch_table_fill(s, (int32_t *)r.tnn.ptr, total, ctx->stream); });
+                       [&] { return launch_table_fill(s, offs_dev, (int)offs.size(), rank_bits, (int32_t *)r.tnn.ptr, total, ctx->stream); });
     }
     if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
     if (e != hipSuccess) {
@@ -1271,8 +1272,8 @@ perch_status perch_set_scene(perch_ctx *ctx, const perch_scene_desc *d, int32_t 
         r.host_labels.assign(d->labels, d->labels + N);
         r.host_depth.assign(d->depth_mm, d->depth_mm + N);
     }
-    r.bytes = r.depth.bytes + r.rgb.bytes + r.labels.bytes + r.opt.bytes + r.olab.bytes + r.kx.bytes
-              + r.ky.bytes + r.ax.bytes + r.ay.bytes + r.thdr.bytes + r.tnn.bytes + r.hstart.bytes + r.hpts.bytes;
+    r.bytes = r.depth.bytes + r.rgb.bytes + r.labels.bytes + r.opt.bytes + r.olab.bytes + r.axes.bytes
+              + r.thdr.bytes + r.tnn.bytes + r.hstart.bytes + r.hpts.bytes;
     std::lock_guard<std::recursive_mutex> lk(ctx->mu);
     ctx->release(tmp);
     ctx->scene_stage.push_back(stg);
@@ -1291,7 +1292,7 @@ perch_status perch_drop_scene(perch_ctx *ctx, int32_t scene_id)
     if (perch_status st = release_check(ctx, true, scene_id)) return st;
     SceneRec &r = it->second;
     FenceRef f = ctx->fence_of(r.uses);
-    for (DevBuf *b : {&r.depth, &r.rgb, &r.labels, &r.opt, &r.olab, &r.kx, &r.ky, &r.ax, &r.ay, &r.thdr, &r.tnn})
+    for (DevBuf *b : {&r.depth, &r.rgb, &r.labels, &r.opt, &r.olab, &r.axes, &r.thdr, &r.tnn})
         ctx->release(*b, f);
     ctx->scenes.erase(it);
     return ok();
