@@ -247,7 +247,7 @@ def main():
     value = n_poses * args.steps / elapsed
 
     # dominant kernel and its roofline
-    score_slots = ["score_lds_small", "score_lds_large", "score_lds_tile", "score_device"]
+    score_slots = ["score_lds_small", "score_lds_large", "score_lds_tile", "score_device", "score_wide"]
     dom = max(score_slots, key=lambda k: prof[k][0])
     dom_ms, dom_launches = prof[dom]
     areas = tile_areas(w)
@@ -266,7 +266,7 @@ def main():
         tile = ar[:, 0]
         for c in range(4):
             class_poses[c] += int((cls == c).sum())
-        sel = cls == cls_idx
+        sel = cls == cls_idx if dom != "score_wide" else cls >= 0     # launches of few poses hold all classes
         ops += float(np.sum(60.0 * m.n_tris + 10.0 * tile[sel] + c_q * L[sel] + c_o * Q[sel]))
         if sel.any():
             byts += float(np.sum(48.0 + 8.0 + ar[sel, 1] * b_pix)) + m.n_verts * 20.0 + m.n_tris * 16.0

@@ -466,9 +466,10 @@ std::vector<int> label_box(SceneRec &r, int32_t label)
 }
 
 // Launches of at most this many poses take the wide path.  Both ways over
-// (class kernels / wide, us a call): 640x480 RGB, 160 poses 595 / 296, 320
-// 630 / 364, 480 642 / 550, 640 670 / 750; 320x240 depth, 128 135 / 86, 400
-// 139 / 119, 512 140 / 138; nearest-neighbour marking, 512 327 / 406.
+// (class kernels / wide, us a call): 640x480 RGB, 160 poses 555 / 293, 320
+// 539 / 361, 480 621 / 543, 640 581 / 746; 320x240 depth, 128 123 / 83, 400
+// 130 / 117, 512 131 / 134; 427x321 6-DoF, 128 132 / 107, 333 137 / 134, 512
+// 137 / 158; nearest-neighbour marking, 512 318 / 400.
 constexpr int kWideMaxPoses = 384;
 // Work-groups its scoring aims at (two per compute unit are resident): more
 // bands shorten the longest one but redo more rows (320x240, 400 poses: 119
