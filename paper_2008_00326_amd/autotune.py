@@ -70,6 +70,16 @@ def choose(trials, min_gain: float = MIN_GAIN) -> dict:
     return trials[0]
 
 
+def _apply(ctx, tuning: dict) -> None:
+    """Sets a kept tuning.  The first candidate spells out the defaults; the
+    context then gets the defaults themselves, under which launches of few
+    poses may still be spread over many work-groups (an explicit tuning always
+    selects the class kernels)."""
+    ctx.set_tuning(None)
+    if tuning != candidates(ctx.tuning(), 1)[0]:
+        ctx.set_tuning(tuning)
+
+
 def _time(ctx, items, reps, stream):
     import torch
     ctx.score_batch(items, stream=stream)            # warm-up (also sizes the buffers)
@@ -113,7 +123,7 @@ def autotune(ctx, items, bucket: str, *, cache_path: str | None = DEFAULT_CACHE,
     key = f"{device_arch()}|{bucket}"
     cache = load_cache(cache_path) if cache_path else {}
     if not force and key in cache:
-        ctx.set_tuning(cache[key]["tuning"])
+        _apply(ctx, cache[key]["tuning"])
         return dict(cache[key], key=key, cached=True)
     stream = stream or torch.cuda.current_stream()
     ctx.set_tuning(None)
@@ -125,7 +135,7 @@ def autotune(ctx, items, bucket: str, *, cache_path: str | None = DEFAULT_CACHE,
         ctx.set_tuning(c)
         trials.append({"tuning": c, "ms": round(_time(ctx, items, reps, stream), 4)})
     best = choose(trials)
-    ctx.set_tuning(best["tuning"])
+    _apply(ctx, best["tuning"])
     fastest = min(trials, key=lambda t: t["ms"])
     rec = {"tuning": best["tuning"], "ms": best["ms"], "trials": trials,
            "default_ms": trials[0]["ms"], "fastest_ms": fastest["ms"],
