@@ -467,59 +467,18 @@ __device__ __forceinline__ void score_pose(const Work &w, int p, uint32_t *tile,
         for (int k = tid; k < min(jpx, band0); k += BLOCK) K::store(keys + k, K::kEmpty);
     }
 
-    // 2. resolve: occluders (Eq. 3) and the downsampling stride
-    int cL = 0;
-    {
-        // tile pixel of index k (clamped into the tile): key and image position
-        auto rpixel = [&](int k, uint32_t &key, int &i, int &j) {
-            const int kc = min(k, tpx - 1);
-            key = k < tpx ? tld<G>(tile + kc) : kEmptyKey;
-            const int ty = tile_row<G>(kc, in.tw, tinv), tx = kc - __mul24(ty, in.tw);
-            i = in.tx0 + tx;
-            j = in.ty0 + ty;
-        };
-        auto resolve = [&](int k, uint32_t key, int i, int j, int dob) {
-            bool keep = false;
-            if (key != kEmptyKey) {
-                const int d = (int)(key >> 16);
-                keep = s.stride == 1 || ((i % s.stride == 0) && (j % s.stride == 0));
-                if (keep && mark && dob > 0 && 16 * dob + s.dq < 16 * d) {
-                    const int pix = j * s.W + i;
-                    if (!(label_mode && s.labels) || s.labels[pix] != it.label) {
-                        keep = false;
-                        if (rf) rf[pix] = 4;
-                    }
-                }
-                if (!keep) tst<G>(tile + k, kEmptyKey);
-            }
-            cL += wave_popc(keep);
-        };
-        // two chunks a turn, both observed depths loaded first (every lane
-        // loads, at a clamped pixel)
-        for (int k0 = 0; k0 < tpx; k0 += 2 * BLOCK) {
-            const int kA = k0 + tid, kB = k0 + BLOCK + tid;
-            uint32_t keyA, keyB;
-            int iA, jA, iB, jB;
-            rpixel(kA, keyA, iA, jA);
-            rpixel(kB, keyB, iB, jB);
-            const int dA = mark ? (int)gld(s.depth + (uint32_t)(jA * s.W + iA)) : 0;
-            const int dB = mark ? (int)gld(s.depth + (uint32_t)(jB * s.W + iB)) : 0;
-            resolve(kA, keyA, iA, jA, dA);
-            if (k0 + BLOCK < tpx) resolve(kB, keyB, iB, jB, dB);
-        }
-    }
     __syncthreads();
 
     // J_o keys held at once: the whole J_o region, or, for a pose of the
     // 1024-thread LDS class whose region does not fit beside its tile, bands
-    // of rows; phases 3 and 4 then run once per band, every inlier marking
+    // of rows; phases 2 to 4 then run once per band, every inlier marking
     // the band's keys, and the J_r counts are taken in the first band.
     int hb = in.jh;
     if (!nnm && !G && !KG && BLOCK == 1024 && in.jw > 0 && tpx + jpx > w.cap_large) hb = (w.cap_large - tpx) / in.jw;
     const int nb = in.jh > 0 ? (in.jh + hb - 1) / hb : 1;
-    int cR = 0, cQ = 0, cO = 0;
+    int cL = 0, cR = 0, cQ = 0, cO = 0;
     const double dl = (double)s.delta;
-    // Phases 3 and 4 run without work-group barriers: each wave takes
+    // Phases 2 to 4 run without work-group barriers: each wave takes
     // 64-pixel blocks in turn and appends its work (inliers to mark and to
     // colour-test, explained observed points to colour-test) to its own
     // queue `q` of 128 entries in LDS, flushed 64 at a time -- a colour
@@ -536,6 +495,9 @@ __device__ __forceinline__ void score_pose(const Work &w, int p, uint32_t *tile,
             __syncthreads();
         }
 
+        // 2. first band: occluders (Eq. 3) and the downsampling stride, in the
+        //    same pass over the tile as phase 3 (a pass of its own: 1.11
+        //    against 1.09 ms for 6,000 nearest-neighbour poses of this class).
         // 3. J_r: nearest observed neighbour from the scene table (or the
         //    kNN II scan).  Queued inliers are colour-tested (Eq. 4, first
         //    band) and mark the observed points they explain.
@@ -603,19 +565,40 @@ __device__ __forceinline__ void score_pose(const Work &w, int p, uint32_t *tile,
             }
         };
         // tile pixel of index k (clamped into the tile): key and image pixel
-        auto tpixel = [&](int k, uint32_t &key, int &pix) {
+        auto tpixel = [&](int k, uint32_t &key, int &pix, bool &grid) {
             const int kc = min(k, tpx - 1);
             key = k < tpx ? tld<G>(tile + kc) : kEmptyKey;
             const int ty = tile_row<G>(kc, in.tw, tinv), tx = kc - __mul24(ty, in.tw);
             pix = (in.ty0 + ty) * s.W + in.tx0 + tx;
+            grid = s.stride == 1 || ((in.tx0 + tx) % s.stride == 0 && (in.ty0 + ty) % s.stride == 0);
         };
-        // four chunks a turn: every chunk's table entries are loaded before
-        // any is queued
+        // four chunks a turn: every chunk's depths and table entries are
+        // loaded before any is queued
         for (int k0 = wave * 64; k0 < tpx; k0 += 4 * BLOCK) {
             uint32_t key[4];
             int pp[4], nn[4];
+            bool grid[4];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) tpixel(k0 + u * BLOCK + lane, key[u], pp[u]);
+            for (int u = 0; u < 4; ++u) tpixel(k0 + u * BLOCK + lane, key[u], pp[u], grid[u]);
+            if (first) {
+                int dob[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) dob[u] = mark ? (int)gld(s.depth + (uint32_t)pp[u]) : 0;
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    bool keep = key[u] != kEmptyKey && grid[u];
+                    if (keep && dob[u] > 0 && 16 * dob[u] + s.dq < 16 * (int)(key[u] >> 16)
+                        && (!(label_mode && s.labels) || s.labels[pp[u]] != it.label)) {
+                        keep = false;
+                        if (rf) rf[pp[u]] = 4;
+                    }
+                    if (key[u] != kEmptyKey && !keep) {
+                        key[u] = kEmptyKey;
+                        tst<G>(tile + k0 + u * BLOCK + lane, kEmptyKey);
+                    }
+                    cL += wave_popc(keep);
+                }
+            }
             if (knn2 || hsh) {
                 auto search = [&](uint32_t key, int pix) {
                     int X, Y, wuv;
