@@ -9,6 +9,7 @@
 #include <rocprofiler-sdk-roctx/roctx.h>
 
 #include <algorithm>
+#include <array>
 #include <atomic>
 #include <cmath>
 #include <cstdarg>
@@ -121,6 +122,11 @@ struct SceneRec {
     std::map<int32_t, std::vector<int>> label_boxes;
     size_t bytes = 0;
     Uses uses;
+    // every device buffer of the scene
+    std::array<DevBuf *, 10> bufs()
+    {
+        return {&depth, &rgb, &labels, &opt, &olab, &axes, &thdr, &tnn, &hstart, &hpts};
+    }
 };
 
 // Allocation granule: 4 KiB up to 1 MiB, then an eighth of the leading
@@ -810,9 +816,7 @@ perch_status perch_destroy(perch_ctx *ctx)
     for (auto &kv : ctx->scenes) {
         SceneRec &r = kv.second;
         FenceRef f = ctx->fence_of(r.uses);
-        for (DevBuf *b : {&r.depth, &r.rgb, &r.labels, &r.opt, &r.olab, &r.axes, &r.thdr,
-                          &r.tnn, &r.hstart, &r.hpts})
-            ctx->release(*b, f);
+        for (DevBuf *b : r.bufs()) ctx->release(*b, f);
     }
     while (!ctx->batches.empty()) perch_batch_destroy(ctx->batches.back());
     for (auto &kv : ctx->work) {
@@ -1127,9 +1131,8 @@ perch_status perch_set_scene(perch_ctx *ctx, const perch_scene_desc *d, int32_t 
     // is not held up
     auto cleanup = [&]() {
         std::lock_guard<std::recursive_mutex> lk(ctx->mu);
-        for (DevBuf *b : {&r.depth, &r.rgb, &r.labels, &r.opt, &r.olab, &r.axes, &r.thdr,
-                          &r.tnn, &r.hstart, &r.hpts, &tmp})
-            ctx->release(*b);
+        for (DevBuf *b : r.bufs()) ctx->release(*b);
+        ctx->release(tmp);
         if (stg) ctx->scene_stage.push_back(stg);
     };
     {
@@ -1288,8 +1291,7 @@ perch_status perch_set_scene(perch_ctx *ctx, const perch_scene_desc *d, int32_t 
                         dev_total);
         }
     }
-    r.bytes = r.depth.bytes + r.rgb.bytes + r.labels.bytes + r.opt.bytes + r.olab.bytes + r.axes.bytes
-              + r.thdr.bytes + r.tnn.bytes + r.hstart.bytes + r.hpts.bytes;
+    for (DevBuf *b : r.bufs()) r.bytes += b->bytes;
     std::lock_guard<std::recursive_mutex> lk(ctx->mu);
     ctx->release(tmp);
     ctx->scene_stage.push_back(stg);
@@ -1308,8 +1310,7 @@ perch_status perch_drop_scene(perch_ctx *ctx, int32_t scene_id)
     if (perch_status st = release_check(ctx, true, scene_id)) return st;
     SceneRec &r = it->second;
     FenceRef f = ctx->fence_of(r.uses);
-    for (DevBuf *b : {&r.depth, &r.rgb, &r.labels, &r.opt, &r.olab, &r.axes, &r.thdr, &r.tnn})
-        ctx->release(*b, f);
+    for (DevBuf *b : r.bufs()) ctx->release(*b, f);
     ctx->scenes.erase(it);
     return ok();
 }
