@@ -454,7 +454,9 @@ perch_status perch_last_classes(perch_ctx *ctx, void *hip_stream, int32_t n, int
  *                 raster tile: 1 = keys in device memory, 2 = keys in LDS,
  *                 one band of rows at a time (0 = 2).
  * With any of these set, launches of few poses go through the footprint
- * classes too instead of spreading each pose over many work-groups.
+ * classes too instead of spreading each pose over many work-groups; a tuning
+ * that equals perch_get_tuning's answer under the defaults in every field is
+ * the defaults, so a saved one can be set again.
  * The setting applies to launches enqueued afterwards, and to batches
  * created afterwards (a batch keeps the setting it was created with).
  * NULL restores the defaults.  perch_get_tuning returns the values in force,

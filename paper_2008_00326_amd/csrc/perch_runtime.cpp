@@ -436,6 +436,19 @@ LaunchCfg launch_cfg(const perch_ctx *ctx)
     return c;
 }
 
+// The tuning in force, defaults resolved.
+perch_tuning resolved_tuning(const perch_ctx *ctx)
+{
+    const LaunchCfg c = launch_cfg(ctx);
+    perch_tuning t{};
+    t.small_block = c.small_block;
+    t.small_words = c.cap_small;
+    for (int k = 0; k < kNumClasses; ++k) t.grid[k] = c.grid[k];
+    t.order = c.sort ? 2 : 1;
+    t.key_bands = c.key_bands ? 2 : 1;
+    return t;
+}
+
 bool finite3(const float *p) { return std::isfinite(p[0]) && std::isfinite(p[1]) && std::isfinite(p[2]); }
 
 }  // namespace
@@ -2047,7 +2060,14 @@ perch_status perch_set_tuning(perch_ctx *ctx, const perch_tuning *t)
         if (t->grid[k] < 0) return fail(PERCH_EINVAL, "grid[%d] must be >= 0", k);
     if (t->order < 0 || t->order > 2) return fail(PERCH_EINVAL, "order must be 0, 1 or 2");
     if (t->key_bands < 0 || t->key_bands > 2) return fail(PERCH_EINVAL, "key_bands must be 0, 1 or 2");
-    ctx->tune = *t;
+    // what perch_get_tuning returns of the defaults is the defaults: a tuning
+    // saved and set again leaves the launches as they were
+    ctx->tune = perch_tuning{};
+    const perch_tuning def = resolved_tuning(ctx);
+    const bool spelled_out = t->small_block == def.small_block && t->small_words == def.small_words
+                             && std::equal(t->grid, t->grid + kNumClasses, def.grid) && t->order == def.order
+                             && t->key_bands == def.key_bands;
+    if (!spelled_out) ctx->tune = *t;
     return ok();
 }
 
@@ -2056,12 +2076,7 @@ perch_status perch_get_tuning(perch_ctx *ctx, perch_tuning *out)
     if (perch_status st = enter(ctx)) return st;
     std::lock_guard<std::recursive_mutex> lk(ctx->mu);
     if (!out) return fail(PERCH_EINVAL, "null output");
-    const LaunchCfg c = launch_cfg(ctx);
-    out->small_block = c.small_block;
-    out->small_words = c.cap_small;
-    for (int k = 0; k < kNumClasses; ++k) out->grid[k] = c.grid[k];
-    out->order = c.sort ? 2 : 1;
-    out->key_bands = c.key_bands ? 2 : 1;
+    *out = resolved_tuning(ctx);
     return ok();
 }
 
