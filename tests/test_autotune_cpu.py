@@ -43,3 +43,54 @@ def test_a_candidate_must_beat_the_default_by_five_per_cent():
     trials.append({"tuning": "c", "ms": 94.0})
     assert autotune.choose(trials)["tuning"] == "c"             # 6 % faster
     assert autotune.choose(trials, min_gain=0.10)["tuning"] == "default"
+
+
+class _Device:
+    """A context whose class kernels take 2 ms by default, 1.8 ms with
+    256-thread work-groups and 1 ms untuned."""
+
+    def __init__(self):
+        self.set = []
+
+    def set_tuning(self, tuning):
+        self.set.append(tuning)
+
+    def tuning(self):
+        return {"small_block": 512, "small_words": 19440, "grid": [512, 256, 256, 64], "order": 2, "key_bands": 2}
+
+    def ms(self):
+        return 1.0 if self.set[-1] is None else (1.8 if self.set[-1]["small_block"] == 256 else 2.0)
+
+
+def _tune(monkeypatch, dev, n_poses, path):
+    import torch
+    monkeypatch.setattr(autotune, "device_arch", lambda device=0: "gfx950")
+    monkeypatch.setattr(autotune, "_time", lambda ctx, items, reps, stream: ctx.ms())
+    monkeypatch.setattr(torch.cuda, "get_device_properties",
+                        lambda d: type("Props", (), {"multi_processor_count": 256}))
+    return autotune.autotune(dev, [{"poses": torch.zeros(n_poses, 12)}], "bucket", cache_path=path, stream=object())
+
+
+def test_the_untuned_launch_is_what_a_candidate_has_to_beat(monkeypatch, tmp_path):
+    """A class-kernel variant faster than the class kernels' defaults but
+    slower than the untuned launch is not kept, timed or from the cache."""
+    path = str(tmp_path / "tune.json")
+    for cached in (False, True):
+        dev = _Device()
+        rec = _tune(monkeypatch, dev, 160, path)
+        assert rec["cached"] == cached
+        assert dev.set[-1] is None
+        assert rec["default_ms"] == rec["ms"] == 1.0 and rec["gain_of_fastest"] == 0.0
+        assert rec["trials"][0]["tuning"] == autotune.candidates(dev.tuning(), 256)[0]
+
+
+def test_records_of_another_launch_size_or_base_are_not_applied(monkeypatch, tmp_path):
+    path = str(tmp_path / "tune.json")
+    old = {"gfx950|bucket": {"tuning": {"small_block": 256, "order": 2, "grid": [0, 0, 0, 0], "small_words": 0}}}
+    autotune.save_cache(old, path)
+    dev = _Device()
+    assert not _tune(monkeypatch, dev, 160, path)["cached"]
+    assert dev.set[-1] is None
+    assert not _tune(monkeypatch, dev, 32000, path)["cached"]
+    assert _tune(monkeypatch, dev, 32100, path)["cached"]
+    assert not _tune(monkeypatch, dev, 161, path)["cached"]
