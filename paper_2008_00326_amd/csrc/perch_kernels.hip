@@ -1496,11 +1496,20 @@ __global__ __launch_bounds__(kWideBlock, 4) void wide_score_kernel(Work w)
                 && (!(label_mode && s.labels) || s.labels[pix] != it.label))
                 keep = false;
             int nn = -1;
+            const bool own = j >= y0 && j < y1;
             if (knn2 || hsh) {
-                if (keep) {
+                // The searches are the launch's cost and go to the band that
+                // counts the point.  A neighbouring band marks from it without
+                // one: a point with no neighbour within delta marks nothing
+                // (640x480, delta 20 mm, 32 poses: hash 22.0 ms with the
+                // searches repeated, 5.3 without; kNN II at 10 mm 357, 103).
+                // J_o by nearest-neighbour marking needs the neighbour itself.
+                if (keep && (own || nnm)) {
                     int X, Y, wuv;
                     mark_params(s, i, j, d, &X, &Y, &wuv);
                     nn = knn2 ? scan_nn(s, X, Y, 16 * d) : hash_nn(s, X, Y, 16 * d);
+                } else if (keep) {
+                    nn = 0;
                 }
             } else {
                 const int e = d - (tr.y & 0xFFFF);
@@ -1508,7 +1517,7 @@ __global__ __launch_bounds__(kWideBlock, 4) void wide_score_kernel(Work w)
                 nn = gld(s.tnn + (uint32_t)(ok ? tr.x + e : 0));
                 if (!ok) nn = -1;
             }
-            const bool own = j >= y0 && j < y1, hit = nn >= 0;
+            const bool hit = nn >= 0;
             cL += wave_popc(keep && own);
             cR += wave_popc(keep && own && !hit);
             if (nnm && !rgb && hit) mark_nn<false>(bits, nn, s.W, in.jx0, by0, in.jw, bh);

@@ -488,8 +488,34 @@ std::vector<int> label_box(SceneRec &r, int32_t label)
 // (class kernels / wide, us a call): 640x480 RGB, 160 poses 555 / 293, 320
 // 539 / 361, 480 621 / 543, 640 581 / 746; 320x240 depth, 128 123 / 83, 400
 // 130 / 117, 512 131 / 134; 427x321 6-DoF, 128 132 / 107, 333 137 / 134, 512
-// 137 / 158; nearest-neighbour marking, 512 318 / 400.
+// 137 / 158.
 constexpr int kWideMaxPoses = 384;
+// The same for a launch with scene s in it.  Work that a band repeats for the
+// rows of its neighbours (s.wty on each side, as far as delta reaches) lowers
+// it for the paper's variants; exact J_o from the table repeats lookups only
+// (delta 40 mm, 384 poses 9547 / 3526; the least gain found is a loss, at
+// stride 2: 333 poses 291 / 291, 384 309 / 331, near candidates 317 / 274).
+//   J_o by nearest-neighbour marking: the class kernels mark one bit per
+//     inlier, a band looks its neighbours' inliers up again (640x480, near
+//     candidates / spread ones: wty 13: 200 poses 138 / 117, 267 / 156; 256
+//     142 / 132, 270 / 194; 384 144 / 188, 274 / 257; wty 38: 160 230 / 221,
+//     368 / 256; 256 230 / 282, 370 / 386; wty 67: 96 247 / 257, 448 / 301; 160
+//     265 / 357, 441 / 437; wty 122: 32 260 / 251, 591 / 288; 96 322 / 434, 597
+//     / 579).
+//   Voxel hash and kNN II with exact J_o, whose searches bands do not repeat
+//     but whose points without a neighbour also go through the marking (hash,
+//     ms, wty 13: 384 poses 7.6 / 5.2; wty 25: 80 18.3 / 16.3, 96 17.7 / 18.9,
+//     256 22.6 / 32.6; wty 52: 100 72 / 45, 384 91 / 112; kNN II, wty 13: 384
+//     882 / 637; wty 52: 128 309 / 310, 384 644 / 859).
+//   Both: every search repeated (hash, ms, wty 13: 100 poses 7.1 / 6.2, 200
+//     7.2 / 8.0; wty 38: 1 15.1 / 14.3, 16 27.5 / 29.9, 52 29.1 / 43.9).
+int wide_max_poses(const SceneDev &s)
+{
+    const bool nn = (s.flags & PERCH_JO_NN) != 0, search = (s.flags & (PERCH_HASH | PERCH_KNN2)) != 0;
+    if (nn && search) return s.wty <= 16 ? 128 : 0;
+    if (nn) return std::min(240, std::max(16, 6000 / s.wty));
+    return search && s.wty > 16 ? 80 : kWideMaxPoses;
+}
 // Work-groups its scoring aims at (two per compute unit are resident): more
 // bands shorten the longest one but redo more rows (320x240, 400 poses: 119
 // us at 1024, 134 at 2048; 640x480, 256 poses of near-truth candidates 323
@@ -506,6 +532,7 @@ struct Built {
     int n_items = 0, n_poses = 0;
     size_t max_pixels = 0;
     int max_tris = 0;
+    int wide_max = kWideMaxPoses;     // the least of its scenes' limits
     bool any_rgb = false;
     bool any_pv = false;   // some scene takes one of the paper's variants (NN marking, kNN II)
     std::vector<int32_t> scene_ids, mesh_ids;
@@ -575,6 +602,7 @@ perch_status build_descriptors(perch_ctx *ctx, const perch_work *req, int32_t n_
         total += q.n_poses;
         b.max_pixels = std::max(b.max_pixels, (size_t)sd.W * sd.H);
         b.max_tris = std::max(b.max_tris, mi->second.dev.nt);
+        b.wide_max = std::min(b.wide_max, wide_max_poses(sd));
         b.any_rgb |= (sd.flags & PERCH_USE_RGB) != 0;
         b.any_pv |= (sd.flags & (PERCH_JO_NN | PERCH_KNN2 | PERCH_HASH)) != 0;
         if (sd.flags & PERCH_KNN1)
@@ -695,7 +723,7 @@ int wide_bands(const perch_ctx *ctx, const Built &b, const LaunchCfg &cfg)
         return 0;
     size_t sw[kNumClasses], sb[kNumClasses], total = 0, tile = 0;
     slot_layout(cfg, b.max_pixels, sw, sb, &total, &tile);
-    if (b.n_poses > kWideMaxPoses || (size_t)b.n_poses * tile > total) return 0;
+    if (b.n_poses > b.wide_max || (size_t)b.n_poses * tile > total) return 0;
     return std::max(1, std::min(kWideGroups / b.n_poses, kWideMaxBands));
 }
 

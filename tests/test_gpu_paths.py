@@ -9,8 +9,10 @@ pytestmark = pytest.mark.gpu
 
 torch = pytest.importorskip("torch")
 
+import oracle  # noqa: E402
 import paper_2008_00326_amd as pk  # noqa: E402
 from random_cases import random_case  # noqa: E402
+from tiny_meshes import box, pose_matrix, rot_x  # noqa: E402
 
 
 def say(msg):
@@ -65,5 +67,47 @@ def test_a_saved_tuning_can_be_set_again(ctx):
     ctx.set_tuning(saved)
     assert ctx.tuning() == saved
     ctx.set_tuning(None)
+    ctx.drop_scene(sid)
+    ctx.unload_mesh(mid)
+
+
+# (scene options, poses of the largest launch that takes the few-poses path)
+LIMITS = [(dict(), 384), (dict(stride=2), 384), (dict(search="hash"), 384), (dict(search="knn2"), 384),
+          (dict(search="hash", delta_mm=30.0), 80), (dict(search="knn2", delta_mm=30.0), 80),
+          (dict(search="hash", delta_mm=30.0, use_rgb=False, mark_occluders=False), 80), (dict(jo="nn"), None),
+          (dict(jo="nn", delta_mm=30.0), None), (dict(jo="nn", delta_mm=90.0, use_rgb=False), None),
+          (dict(search="hash", jo="nn"), 128), (dict(search="hash", jo="nn", delta_mm=30.0), 0),
+          (dict(search="knn2", jo="nn", delta_mm=30.0), 0)]
+
+
+@pytest.mark.parametrize("form,limit", LIMITS, ids=lambda v: "-".join(f"{a}={b}" for a, b in v.items()) if isinstance(v, dict) else str(v))
+def test_either_side_of_a_scene_s_limit(ctx, form, limit):
+    """What a band repeats of its neighbours' rows lowers the limit of the
+    few-poses path: the path on either side of it, the same results."""
+    K = (160, 120, 300.0, 300.0, 80.0, 60.0)
+    mesh = box((-30, -20, -25), (30, 20, 25), n=4, rgb_seed=3)
+    gt = pose_matrix(rot_x(0.4), (8, -5, 520))
+    depth, _, rgb = oracle.render(mesh, gt, K)
+    depth = np.where(depth > 0, depth, 620).astype(np.uint16)
+    kw = {"delta_mm": 3.0, "tau_c": 20.0, "use_rgb": True, **form}
+    sid = ctx.set_scene(K, depth, rgb, **kw)
+    mid = ctx.load_mesh(mesh.xyz, mesh.tri, mesh.rgb)
+    wty = ctx.scene_info(sid)["window_y"]
+    if limit is None:
+        limit = min(240, max(16, 6000 // wty))
+    elif form.get("search"):
+        assert (wty > 16) == ("delta_mm" in form)       # the rule's two sides
+    say(f"limit {form}: {limit} poses, window {wty}")
+    rng = np.random.default_rng(limit)
+    many = np.stack([gt] * (limit + 1)).astype(np.float32)
+    many[:, [3, 7, 11]] += rng.normal(0, 8, (limit + 1, 3)).astype(np.float32)
+    ref, wide = score(ctx, sid, mid, many, {"order": 2})
+    assert not wide
+    for n in (limit, limit + 1):
+        if n == 0:
+            continue
+        out, wide = score(ctx, sid, mid, many[:n], None)
+        assert wide == (n <= limit)
+        assert all(np.array_equal(a, b[:n]) for a, b in zip(out, ref))
     ctx.drop_scene(sid)
     ctx.unload_mesh(mid)
