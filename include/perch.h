@@ -431,8 +431,9 @@ perch_status perch_profile_read(perch_ctx *ctx, int32_t n_slots, double *total_m
 
 /* Footprint class (0..3, the scoring slots 1..4 of the profiler) that the
  * last perch_score_poses call on hip_stream assigned to each of its n poses
- * (a launch of few poses, slot 12, assigns them too):
- * class_host[i] for pose i.  Blocks until that call has finished.  Meant for
+ * (a launch of few poses, slot 12, assigns them too, though its kernels serve
+ * every class): class_host[i] for pose i.  Which kernels ran is told by the
+ * profiler's slots.  Blocks until that call has finished.  Meant for
  * inspection and work accounting. */
 perch_status perch_last_classes(perch_ctx *ctx, void *hip_stream, int32_t n, int32_t *class_host);
 

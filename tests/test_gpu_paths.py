@@ -1,5 +1,6 @@
 """Which kernels score a launch: the profiler's slots tell the few-poses path
-(each pose spread over many work-groups) from the footprint-class kernels."""
+(each pose spread over many work-groups) from the footprint-class kernels, and
+each is compared with the oracle where it is known to have run."""
 import sys
 
 import numpy as np
@@ -11,8 +12,11 @@ torch = pytest.importorskip("torch")
 
 import oracle  # noqa: E402
 import paper_2008_00326_amd as pk  # noqa: E402
+from paper_2008_00326_amd.workloads import make_config  # noqa: E402
 from random_cases import random_case  # noqa: E402
-from tiny_meshes import box, pose_matrix, rot_x  # noqa: E402
+from tiny_meshes import TScene, box, pose_matrix, rot_x  # noqa: E402
+
+PATHS = [(None, True), ({"order": 2}, False), ({"small_block": 256, "key_bands": 1}, False)]   # (tuning, few-poses path)
 
 
 def say(msg):
@@ -111,3 +115,102 @@ def test_either_side_of_a_scene_s_limit(ctx, form, limit):
         assert all(np.array_equal(a, b[:n]) for a, b in zip(out, ref))
     ctx.drop_scene(sid)
     ctx.unload_mesh(mid)
+
+
+def oracle_flags(rgb, occl=True, volume="aabb", jo="exact"):
+    return ((oracle.USE_RGB if rgb else 0) | (oracle.MARK_OCCLUDERS if occl else 0)
+            | (oracle.VOL_CYL if volume == "cyl" else 0) | (oracle.JO_NN if jo == "nn" else 0))
+
+
+def check(got, exp, rgb, jo, what):
+    """L and Q equal, without the colour term J_r and J_o too; with it, whose
+    decisions are binary32, within a thousandth of the points tested."""
+    assert np.array_equal(got[2], exp[2]) and np.array_equal(got[3], exp[3]), what
+    if not rgb:
+        assert np.array_equal(got[0], exp[0]) and np.array_equal(got[1], exp[1]), what
+        return
+    tol_r = np.ceil(0.001 * exp[2])
+    assert np.all(np.abs(got[0] - exp[0]) <= tol_r), what
+    assert np.all(np.abs(got[1] - exp[1]) <= np.ceil(0.001 * exp[3]) + (tol_r if jo == "nn" else 0)), what
+
+
+@pytest.mark.parametrize("form", [dict(), dict(volume="cyl"), dict(jo="nn"), dict(jo="nn", volume="cyl"),
+                                  dict(search="hash"), dict(search="knn2"), dict(search="hash", jo="nn")],
+                         ids=lambda f: "-".join(f.values()) or "default")
+@pytest.mark.parametrize("seed", range(6))
+def test_each_path_matches_the_oracle(ctx, seed, form):
+    mesh, scene, poses, p = random_case(60 + seed)
+    poses = poses[:24]
+    sid = ctx.set_scene(scene.K, scene.depth, scene.rgb, delta_mm=p["delta"], tau_c=p["tau"], use_rgb=p["rgb"],
+                        mark_occluders=p["occl"], stride=p["stride"], **form)
+    mid = ctx.load_mesh(mesh.xyz, mesh.tri, mesh.rgb)
+    jo = form.get("jo", "exact")
+    exp = oracle.score(mesh, scene, poses, delta_mm=p["delta"], tau_c=p["tau"], stride=p["stride"], threads=16,
+                       flags=oracle_flags(p["rgb"], p["occl"], form.get("volume", "aabb"), jo))
+    wty = ctx.scene_info(sid)["window_y"]
+    for tuning, few in PATHS:
+        say(f"case {60 + seed} {form} {tuning} wty {wty}")
+        got, wide = score(ctx, sid, mid, poses, tuning)
+        assert wide == (few and not (jo == "nn" and "search" in form and wty > 16))
+        check(got, exp, p["rgb"], jo, (seed, form, tuning))
+    ctx.drop_scene(sid)
+    ctx.unload_mesh(mid)
+    assert exp[2].sum() > 0
+
+
+@pytest.mark.parametrize("form", [dict(), dict(use_rgb=False), dict(jo="nn"), dict(search="hash", use_rgb=False)],
+                         ids=lambda f: "-".join(str(v) for v in f.values()) or "default")
+def test_tiles_beyond_the_lds_by_the_class_kernels(ctx, form):
+    """Poses whose tile and keys no LDS holds, scored by the kernel of the
+    device-memory class and by the few-poses path: the oracle's counts."""
+    K = (320, 240, 262.5, 262.5, 160.0, 120.0)
+    cube = box((-100, -100, -100), (100, 100, 100), n=6, rgb_seed=8)
+    P0 = pose_matrix(np.eye(3), (10, -5, 420))
+    d, _, c = oracle.render(cube, P0, K)
+    kw = {"use_rgb": True, **form}
+    sid = ctx.set_scene(K, d, c, delta_mm=10.0, tau_c=20.0, **kw)
+    mid = ctx.load_mesh(cube.xyz, cube.tri, cube.rgb)
+    poses = np.stack([P0, pose_matrix(np.eye(3), (14, -2, 415)), pose_matrix(np.eye(3), (0, 0, 330)),
+                      pose_matrix(np.eye(3), (-20, 10, 700))])
+    jo = form.get("jo", "exact")
+    exp = oracle.score(cube, TScene(K, d, c, None), poses, delta_mm=10.0, tau_c=20.0, threads=16,
+                       flags=oracle_flags(kw["use_rgb"], jo=jo))
+    for tuning, few in PATHS[:2]:
+        say(f"beyond the LDS {form} {tuning}")
+        got, wide = score(ctx, sid, mid, poses, tuning)
+        assert wide == few
+        assert 3 in ctx.last_classes(len(poses)).tolist()
+        check(got, exp, kw["use_rgb"], jo, (form, tuning))
+    ctx.drop_scene(sid)
+    ctx.unload_mesh(mid)
+
+
+@pytest.mark.parametrize("jo", ["exact", "nn"])
+def test_poses_of_each_class_by_the_class_kernels(ctx, jo):
+    """640x480 RGB: poses of every footprint class that the full launch
+    assigns, scored a few at a time by the class kernels and by the few-poses
+    path, against the oracle and the full launch."""
+    w = make_config(2, 0)
+    s = w.scene
+    sid = ctx.set_scene(s.K, s.depth, s.rgb, delta_mm=w.delta_mm, tau_c=w.tau_c, use_rgb=True, jo=jo)
+    rng = np.random.default_rng(17)
+    seen = set()
+    for o in w.objects[:3]:
+        m = w.meshes[o.mesh]
+        mid = ctx.load_mesh(m.xyz, m.tri, m.rgb)
+        full, wide = score(ctx, sid, mid, o.poses, {"key_bands": 1}, label=o.label)
+        assert not wide
+        cls = ctx.last_classes(len(o.poses))
+        seen |= set(cls.tolist())
+        sel = np.concatenate([rng.choice(np.flatnonzero(cls == k), 2) for k in np.unique(cls)])
+        exp = oracle.score(m, TScene(s.K, s.depth, s.rgb, None), o.poses[sel], delta_mm=w.delta_mm, tau_c=w.tau_c,
+                           flags=oracle_flags(True, w.mark_occluders, jo=jo), label=o.label, threads=16)
+        for tuning, few in PATHS:
+            say(f"each class, {jo}, object {o.label}, {tuning}")
+            got, wide = score(ctx, sid, mid, o.poses[sel], tuning, label=o.label)
+            assert wide == few
+            check(got, exp, True, jo, (o.label, tuning))
+            assert all(np.array_equal(a, b[sel]) for a, b in zip(got, full))
+        ctx.unload_mesh(mid)
+    ctx.drop_scene(sid)
+    assert seen >= ({0, 1, 2} if jo == "exact" else {0, 1})
