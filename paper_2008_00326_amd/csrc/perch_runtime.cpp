@@ -76,12 +76,19 @@ perch_status ok()
     return PERCH_OK;
 }
 
+// A HIP error that a status reports, or that a second attempt follows, is
+// taken off the thread: HIP keeps it as the last error until it is read, and
+// the next launch's check (this library's or the caller's) would report it.
+void reported() { (void)hipGetLastError(); }
+
 #define HIP_TRY(expr)                                                                              \
     do {                                                                                           \
         hipError_t e_ = (expr);                                                                    \
-        if (e_ != hipSuccess)                                                                      \
+        if (e_ != hipSuccess) {                                                                    \
+            reported();                                                                            \
             return fail(e_ == hipErrorOutOfMemory ? PERCH_ENOMEM : PERCH_EDEVICE, "%s: %s", #expr, \
                         hipGetErrorString(e_));                                                    \
+        }                                                                                          \
     } while (0)
 
 struct DevBuf {
@@ -313,12 +320,15 @@ struct perch_ctx {
         void *p = nullptr;
         hipError_t e = hipMalloc(&p, bytes);
         if (e == hipErrorOutOfMemory && !cache.empty()) {
+            reported();
             trim();
             e = hipMalloc(&p, bytes);
         }
-        if (e != hipSuccess)
+        if (e != hipSuccess) {
+            reported();
             return fail(e == hipErrorOutOfMemory ? PERCH_ENOMEM : PERCH_EDEVICE, "hipMalloc(%zu): %s", bytes,
                         hipGetErrorString(e));
+        }
         b.ptr = p;
         b.bytes = bytes;
         used += bytes;
@@ -1221,6 +1231,7 @@ perch_status perch_set_scene(perch_ctx *ctx, const perch_scene_desc *d, int32_t 
         if (e == hipSuccess) stg->bytes = stage_bytes;
     }
     if (e != hipSuccess) {
+        reported();
         cleanup();
         return fail(PERCH_ENOMEM, "pinned staging of %zu bytes: %s", stage_bytes, hipGetErrorString(e));
     }
@@ -2162,6 +2173,7 @@ perch_status perch_batch_create(perch_ctx *ctx, int32_t max_items, int32_t max_p
     b->cfg = launch_cfg(ctx);
     auto cleanup = [&](perch_status st, const char *what, hipError_t e) {
         std::string msg = e != hipSuccess ? std::string(what) + ": " + hipGetErrorString(e) : g_last_error;
+        if (e != hipSuccess) reported();
         for (DevBuf *d : {&b->lb.desc, &b->lb.info, &b->lb.lists, &b->lb.counts, &b->lb.scratch, &b->lb.best,
                           &b->lb.lab})
             ctx->release(*d);

@@ -10,6 +10,7 @@ pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
 import paper_2008_00326_amd as pk  # noqa: E402
+from tiny_meshes import box, pose_matrix  # noqa: E402
 
 
 def say(msg):
@@ -40,3 +41,24 @@ def test_dropped_scenes_give_their_memory_back(search, labels):
             sid = ctx.set_scene(K, depth, rgb, lab, delta_mm=5.0, search=search)
             assert ctx.scene_info(sid)["device_bytes"] == size
             ctx.drop_scene(sid)
+
+
+def test_a_refused_allocation_is_reported_once():
+    """Scratch that no device holds is refused; the calls after it, the
+    library's and torch's on the same thread, do not report it again."""
+    K = (64, 48, 60.0, 60.0, 32.0, 24.0)
+    cube = box((-30, -30, -30), (30, 30, 30), n=2)
+    d = np.full((48, 64), 500, np.uint16)
+    say("refused allocation")
+    with pk.Context(0) as ctx:
+        sid = ctx.set_scene(K, d, delta_mm=5.0)
+        mid = ctx.load_mesh(cube.xyz, cube.tri)
+        t = torch.from_numpy(np.stack([pose_matrix(np.eye(3), (0, 0, 520))] * 5).astype(np.float32)).cuda()
+        ref = torch.stack(ctx.score_poses(sid, mid, t)).cpu()
+        with pytest.raises(pk.PerchError) as e:
+            ctx.batch(1, 1, (1 << 31) - 1)               # some 6 TB of device-memory slots
+        assert e.value.status == -2, e.value
+        assert torch.equal(torch.stack(ctx.score_poses(sid, mid, t)).cpu(), ref)
+        with pytest.raises(pk.PerchError):
+            ctx.batch(1, 1, (1 << 31) - 1)
+        assert float((t + 1.0).sum()) == pytest.approx(float(t.double().sum()) + t.numel(), rel=1e-5)
