@@ -198,6 +198,7 @@ struct perch_ctx {
     // released device blocks awaiting reuse, and recycled use-tracking events
     std::vector<CachedBlock> cache;
     size_t cached = 0;
+    size_t refused = SIZE_MAX;            // the smallest block the driver refused since memory last went back to it
     std::vector<hipEvent_t> ev_pool;
 
     // profiler: HIP events around each launch, on the launch stream
@@ -293,6 +294,7 @@ struct perch_ctx {
         }
         cache.clear();
         cached = 0;
+        refused = SIZE_MAX;
     }
     perch_status alloc(DevBuf &b, size_t bytes)
     {
@@ -326,6 +328,7 @@ struct perch_ctx {
         }
         if (e != hipSuccess) {
             reported();
+            if (e == hipErrorOutOfMemory) refused = std::min(refused, bytes);
             return fail(e == hipErrorOutOfMemory ? PERCH_ENOMEM : PERCH_EDEVICE, "hipMalloc(%zu): %s", bytes,
                         hipGetErrorString(e));
         }
@@ -358,6 +361,31 @@ struct perch_ctx {
             release(b);
         }
         return alloc(b, bytes);
+    }
+    // Would ensure(b, bytes) succeed, as far as is known without a wait or an
+    // allocation: from the budget, and from what the driver refused before.
+    bool fits(const DevBuf &b, size_t bytes) const
+    {
+        if (b.bytes >= bytes && b.ptr) return true;
+        const size_t want = round_alloc(bytes == 0 ? 256 : bytes);
+        return want < refused && (!budget || used - b.bytes + want <= budget);
+    }
+    // Scratch of a persistent launch, whose work-groups share it out whatever
+    // their number: the first size that fits, from the one wanted down.
+    // bytes(k) is the size of the k-th choice, 0 past the last.  A choice that
+    // is known not to fit is passed over, so that a launch which settled for
+    // less neither waits nor gives its buffer back the next time.
+    template <class Bytes>
+    perch_status ensure_first(DevBuf &b, int *choice, Bytes bytes)
+    {
+        for (int k = 0;; ++k) {
+            const size_t want = bytes(k);
+            const bool last = bytes(k + 1) == 0;
+            if (!last && !fits(b, want)) continue;
+            const perch_status s = ensure(b, want);
+            *choice = k;
+            if (s != PERCH_ENOMEM || last) return s;
+        }
     }
 };
 
@@ -1642,17 +1670,21 @@ perch_status perch_refine_poses(perch_ctx *ctx, int32_t scene_id, int32_t mesh_i
     // them, so that one works while the other waits at a barrier or for its
     // update on one thread (1,600 poses: 2.63 ms against 2.86 with one of
     // 1024); below that a pose takes a whole compute unit, as it does where
-    // the scratch of twice the work-groups does not fit.
+    // the scratch of twice the work-groups does not fit; then ever fewer.
     const int cu = std::max(ctx->n_cu, 1);
-    int block = n > cu ? 512 : 1024;
-    int grid = std::min(n, block == 512 ? 2 * cu : cu);
-    perch_status fit = ctx->ensure(b.icp, pts_at(grid) + (size_t)grid * slots * pts * sizeof(int4));
-    if (fit == PERCH_ENOMEM && block == 512) {
-        block = 1024;
-        grid = cu;
-        fit = ctx->ensure(b.icp, pts_at(grid) + (size_t)grid * slots * pts * sizeof(int4));
-    }
-    if (fit) return fit;
+    struct Shape {
+        int block, grid;
+    };
+    std::vector<Shape> shapes;
+    if (n > cu) shapes.push_back({512, std::min(n, 2 * cu)});
+    for (int g = std::min(n, cu); g > 0; g /= 2) shapes.push_back({1024, g});
+    int choice = 0;
+    if (perch_status e = ctx->ensure_first(b.icp, &choice, [&](int k) {
+            if (k >= (int)shapes.size()) return (size_t)0;
+            return pts_at(shapes[k].grid) + (size_t)shapes[k].grid * slots * pts * sizeof(int4);
+        }))
+        return e;
+    const int block = shapes[choice].block, grid = shapes[choice].grid;
     const size_t pts_off = pts_at(grid);
     IcpArgs a{};
     a.s = s;
@@ -1793,9 +1825,14 @@ perch_status perch_msg_expand(perch_ctx *ctx, int32_t scene_id, const perch_plac
     StreamBufs &b = ctx->work[st];
     const SceneDev &s = sr.dev;
     const size_t px = (size_t)s.W * s.H;
-    const int grid = std::max(1, std::min(n, std::max(ctx->n_cu, 1)));
+    int grid = std::max(1, std::min(n, std::max(ctx->n_cu, 1)));
+    int choice = 0;       // fewer work-groups with tiles where they do not fit
+    if (perch_status e = ctx->ensure_first(b.msg, &choice, [&](int k) {
+            return grid >> k == 0 ? (size_t)0 : msg_layout(px, grid >> k, 1, (size_t)n_state, 1, 0).bytes;
+        }))
+        return e;
+    grid >>= choice;
     const MsgLayout l = msg_layout(px, grid, 1, (size_t)n_state, 1, 0);
-    if (perch_status e = ctx->ensure(b.msg, l.bytes)) return e;
     if (perch_status e = ctx->ensure(b.msg_states[0], msg_state_bytes(px))) return e;
     char *base = (char *)b.msg.ptr;
     const bool rgb = (s.flags & PERCH_USE_RGB) != 0;
@@ -1851,13 +1888,11 @@ perch_status perch_msg_search(perch_ctx *ctx, int32_t scene_id, const perch_msg_
     if (si == ctx->scenes.end()) return fail(PERCH_ENOTFOUND, "unknown scene id %d", scene_id);
     SceneRec &sr = si->second;
     if (perch_status e = msg_check_scene(sr)) return e;
-    size_t max_n = 0;
     for (int o = 0; o < n_obj; ++o) {
         if (!ctx->meshes.count(objects[o].mesh_id))
             return fail(PERCH_ENOTFOUND, "unknown mesh id %d", objects[o].mesh_id);
         if (objects[o].n_poses < 0 || (objects[o].n_poses > 0 && !objects[o].poses_dev))
             return fail(PERCH_EINVAL, "object %d: bad poses", o);
-        max_n = std::max(max_n, (size_t)objects[o].n_poses);
     }
     for (int l = 0; l < n_obj; ++l) order_host[l] = pose_host[l] = -1;
     *cost_host = -1;
@@ -1886,17 +1921,20 @@ perch_status perch_msg_search(perch_ctx *ctx, int32_t scene_id, const perch_msg_
         for (const Node &nd : cur)
             for (int o = 0; o < n_obj; ++o)
                 if (!(nd.placed >> o & 1u)) total += (size_t)objects[o].n_poses;
+        // where it does not fit, one object appended at a time, then fewer work-groups with tiles
         int grid = (int)std::min<size_t>(std::max<size_t>(total, 1), cu);
         size_t adds = level + 1 < n_obj ? (beam > 0 ? std::min(beam, kMsgAdds) : kMsgAdds) : 1;
-        MsgLayout l = msg_layout(px, grid, adds, 0, cur.size() * (size_t)n_obj, total);
-        perch_status fit = ctx->ensure(b.msg, l.bytes);
-        if (fit == PERCH_ENOMEM) {     // fewer work-groups with tiles, one object appended at a time
-            grid = (int)std::min<size_t>(std::max<size_t>(max_n, 1), grid);
-            adds = 1;
-            l = msg_layout(px, grid, adds, 0, cur.size() * (size_t)n_obj, total);
-            fit = ctx->ensure(b.msg, l.bytes);
-        }
-        if (fit) return fit;
+        auto layout = [&](int k) {
+            return msg_layout(px, k < 2 ? grid : grid >> (k - 1), k == 0 ? adds : 1, 0, cur.size() * (size_t)n_obj, total);
+        };
+        int choice = 0;
+        if (perch_status e = ctx->ensure_first(b.msg, &choice, [&](int k) {
+                return k >= 2 && grid >> (k - 1) == 0 ? (size_t)0 : layout(k).bytes;
+            }))
+            return e;
+        const MsgLayout l = layout(choice);
+        if (choice > 0) adds = 1;
+        if (choice > 1) grid >>= choice - 1;
         char *base = (char *)b.msg.ptr;
         int32_t *outd = (int32_t *)(base + l.out);
         size_t off = 0;

@@ -9,8 +9,9 @@ pytestmark = pytest.mark.gpu
 
 torch = pytest.importorskip("torch")
 
+import oracle  # noqa: E402
 import paper_2008_00326_amd as pk  # noqa: E402
-from tiny_meshes import box, pose_matrix  # noqa: E402
+from tiny_meshes import box, pose_matrix, rot_x  # noqa: E402
 
 
 def say(msg):
@@ -62,3 +63,71 @@ def test_a_refused_allocation_is_reported_once():
         with pytest.raises(pk.PerchError):
             ctx.batch(1, 1, (1 << 31) - 1)
         assert float((t + 1.0).sum()) == pytest.approx(float(t.double().sum()) + t.numel(), rel=1e-5)
+
+
+def _table_top():
+    K = (320, 240, 262.5, 262.5, 160.0, 120.0)
+    mesh = box((-40, -30, -25), (40, 30, 25), n=4, rgb_seed=2)
+    gt = pose_matrix(rot_x(0.5), (6, -4, 700))
+    d, _, c = oracle.render(mesh, gt, K)
+    d = np.where(d > 0, d, 800).astype(np.uint16)
+    return K, mesh, gt, d, c
+
+
+def _around(gt, n, seed):
+    P = np.stack([gt] * n).astype(np.float32)
+    P[:, [3, 7, 11]] += np.random.default_rng(seed).normal(0, 6, (n, 3)).astype(np.float32)
+    return torch.from_numpy(P).cuda()
+
+
+@pytest.mark.parametrize("method,dof", [("point", 3), ("plane", 6)])
+@pytest.mark.parametrize("megabytes", [None, 1200, 300, 60])
+def test_refinement_in_less_scratch(method, dof, megabytes):
+    """600 poses at stride 1 want 1.4 GB of scratch (GICP 2.0): with a budget
+    of less the results are the same, and a call after the first one queues
+    its work without waiting for the device."""
+    K, mesh, gt, d, _ = _table_top()
+    say(f"refine within {megabytes} MB, {method}")
+    kw = dict(rho_mm=15.0, iterations=4, stride=1, dof=dof, method=method)
+    with pk.Context(0) as ctx:
+        sid, mid = ctx.set_scene(K, d, delta_mm=8.0), ctx.load_mesh(mesh.xyz, mesh.tri)
+        t = _around(gt, 600, 3)
+        ref = [x.cpu() for x in ctx.refine_poses(sid, mid, t, **kw)]
+    with pk.Context(0, hbm_budget_bytes=(megabytes or 8000) << 20) as ctx:
+        sid, mid = ctx.set_scene(K, d, delta_mm=8.0), ctx.load_mesh(mesh.xyz, mesh.tri)
+        for _ in range(2):
+            assert all(torch.equal(a.cpu(), b) for a, b in zip(ctx.refine_poses(sid, mid, t, **kw), ref))
+        # other work of some tens of milliseconds, on a stream of its own
+        a = torch.ones(8192, 8192, device="cuda")
+        side, done = torch.cuda.Stream(), torch.cuda.Event()
+        torch.mm(a, a)
+        torch.cuda.synchronize()
+        with torch.cuda.stream(side):
+            for _ in range(8):
+                torch.mm(a, a)
+            done.record()
+        got = ctx.refine_poses(sid, mid, t, **kw)
+        assert not done.query()
+        assert all(torch.equal(a.cpu(), b) for a, b in zip(got, ref))
+        torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("megabytes", [None, 100, 60, 24])
+def test_tree_in_less_scratch(megabytes):
+    """The tree's levels and a state's successors with fewer work-groups and
+    one object appended at a time: the same answer."""
+    K, mesh, gt, d, c = _table_top()
+    say(f"tree within {megabytes} MB")
+    far = gt.copy()
+    far[3] += 150.0
+    res = []
+    for budget in (0, (megabytes or 8000) << 20):
+        with pk.Context(0, hbm_budget_bytes=budget) as ctx:
+            sid = ctx.set_scene(K, d, c, delta_mm=8.0, tau_c=20.0, search="hash")
+            mid = ctx.load_mesh(mesh.xyz, mesh.tri, mesh.rgb)
+            polys = [_around(gt, 150, 5), _around(far, 150, 6)]
+            best = ctx.msg_search(sid, [(mid, k, p) for k, p in enumerate(polys)], beam=3)
+            e = ctx.msg_expand(sid, [(mid, 0, gt)], mid, polys[1], label=1)
+            res.append((best, [x.cpu().numpy() for x in e if x is not None]))
+    assert str(res[0][0]) == str(res[1][0])
+    assert all(np.array_equal(x, y) for x, y in zip(res[0][1], res[1][1]))
