@@ -1990,7 +1990,8 @@ __global__ __launch_bounds__(256) void table_fill_near_kernel(SceneDev s, const 
 
 // Offsets of the windows of a scene for table_fill_near_kernel, nearest
 // first; empty where the general fill has to do the work: windows that no
-// list holds, a key that 32 bits don't, whole numbers that binary32 doesn't.
+// list holds, a key that 32 bits don't, whole numbers that binary32 doesn't,
+// pixels far from square.
 void table_fill_offsets(const SceneDev &s, std::vector<int2> *out, int *bits)
 {
     out->clear();
@@ -2002,8 +2003,10 @@ void table_fill_offsets(const SceneDev &s, std::vector<int2> *out, int *bits)
     const double kmax = 16.0 * 65536.0 * std::max({std::fabs(0.0 - s.cx) / s.fx, std::fabs(s.W - 1.0 - s.cx) / s.fx,
                                                     std::fabs(0.0 - s.cy) / s.fy, std::fabs(s.H - 1.0 - s.cy) / s.fy});
     if (!(kmax < 1 << 24)) return;
-    // a counting sort by whole pixels of distance
+    // a counting sort by whole pixels of distance, whose counts grow with fx /
+    // fy: pixels far from square (beyond any camera's) are left to the general fill
     const double c = (double)s.fx / (double)s.fy;
+    if (!(std::sqrt((double)s.wtx * s.wtx + c * c * s.wty * s.wty) < kFillOffsMax)) return;
     auto ring = [&](int dx, int dy) { return (int)(std::sqrt(dx * dx + c * c * dy * dy) * (1.0 - 1e-9)); };
     std::vector<int> at(ring(s.wtx, s.wty) + 2, 0);
     for (int dy = -s.wty; dy <= s.wty; ++dy)

@@ -13,7 +13,7 @@ pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
 import paper_2008_00326_amd as pk  # noqa: E402
-from tiny_meshes import box, pose_matrix, rot_x  # noqa: E402
+from tiny_meshes import TScene, box, pose_matrix, rot_x  # noqa: E402
 
 
 def say(msg):
@@ -56,3 +56,26 @@ def test_table_equals_hash(kind, delta, size):
         assert np.array_equal(out[0], out[1]), (jo, out[0] - out[1])
     c.unload_mesh(mid)
     c.close()
+
+
+@pytest.mark.parametrize("fy", [0.13, 40.0])
+def test_pixels_far_from_square(fy):
+    """A focal length in x of millions of pixels, in y of a fraction of one:
+    the table is filled without a list of offsets as long as their ratio."""
+    import oracle
+    K = (4096, 4, 2.3e8, fy, 0.0, 2.0)
+    rng = np.random.default_rng(5)
+    d = rng.integers(64999, 65002, (4, 4096)).astype(np.uint16)
+    d[:, 1000:] = 0
+    mesh = box((0.05, -9e5, -0.5), (1.0, 9e5, 0.5), n=1)
+    poses = np.stack([pose_matrix(np.eye(3), (0.01 * k, 0.0, 65000.0 + 0.5 * k)) for k in range(3)]).astype(np.float32)
+    exp = oracle.score(mesh, TScene(K, d), poses, delta_mm=0.2, flags=oracle.MARK_OCCLUDERS, threads=8, search="window")
+    assert exp[2].min() > 1000 and (0 < exp[0]).any() and (exp[0] < exp[2]).any()
+    t = torch.from_numpy(poses).cuda()
+    for search in ("table", "hash"):
+        say(f"pixels of 1 : {2.3e8 / fy:.2g}, {search}")
+        with pk.Context(0) as c:
+            mid = c.load_mesh(mesh.xyz, mesh.tri)
+            sid = c.set_scene(K, d, delta_mm=0.2, search=search)
+            got = [x.cpu().numpy() for x in c.score_poses(sid, mid, t)]
+        assert all(np.array_equal(a, b) for a, b in zip(got, exp)), (search, got, exp)
