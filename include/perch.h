@@ -318,9 +318,9 @@ typedef struct {
  *   iters_dev:   n int32 updates applied, or NULL
  *   matched_dev: n int32 matches in the last iteration examined, or NULL
  * Asynchronous on hip_stream.  Device scratch of the stream: the target in
- * tiles (20 bytes a pixel) and, per work-group (two per compute unit, fewer
- * where they do not fit; at most n), a W*H tile and 2 (GICP: 3) lists of the
- * stride grid's points. */
+ * tiles (20 bytes a pixel) and, per work-group (one per compute unit, two for
+ * more than four poses each, fewer where they do not fit; at most n), a W*H
+ * tile and 2 (GICP: 3) lists of the stride grid's points. */
 perch_status perch_refine_poses(perch_ctx *ctx, int32_t scene_id, int32_t mesh_id, int32_t label,
                                 const float *poses_dev, int32_t n, const perch_icp_params *params,
                                 float *refined_dev, int32_t *iters_dev, int32_t *matched_dev,

@@ -1666,17 +1666,22 @@ perch_status perch_refine_poses(perch_ctx *ctx, int32_t scene_id, int32_t mesh_i
     const size_t tiles_off = target_off + icp_tiles(s.W, s.H) * 16 * sizeof(int4);
     const int slots = prm->method == PERCH_ICP_PLANE ? 3 : 2;   // source, mapped (+ normals for GICP)
     auto pts_at = [&](int groups) { return (tiles_off + (size_t)groups * px * 4 + 255) & ~(size_t)255; };
-    // Two 512-thread work-groups per compute unit once there are poses for
-    // them, so that one works while the other waits at a barrier or for its
-    // update on one thread (1,600 poses: 2.63 ms against 2.86 with one of
-    // 1024); below that a pose takes a whole compute unit, as it does where
-    // the scratch of twice the work-groups does not fit; then ever fewer.
+    // Two 512-thread work-groups per compute unit for many poses, so that one
+    // works while the other waits at a barrier or for its update on one
+    // thread; below that a pose takes a whole compute unit and with it half the
+    // time, as it does where the scratch of twice the work-groups does not
+    // fit; then ever fewer.  ms with one / two work-groups, 640x480, objects of
+    // 38k, 12k and 3k pixels: 300 poses 7.7 / 9.9, 1.53 / 2.03; 512 10.4 /
+    // 11.7, 2.24 / 2.35, 0.75 / 0.76; 1,024 14.8 / 16.4, 3.47 / 3.68, 1.20 /
+    // 1.17; 1,280 19.1 / 20.1, 4.43 / 4.29, 1.54 / 1.42; 2,048 26.2 / 26.2, 6.62
+    // / 6.31, 2.31 / 2.03.  What holds the larger object back is its search,
+    // not its tile beyond the halved LDS (20,064 pixels: 11.8 / 12.1).
     const int cu = std::max(ctx->n_cu, 1);
     struct Shape {
         int block, grid;
     };
     std::vector<Shape> shapes;
-    if (n > cu) shapes.push_back({512, std::min(n, 2 * cu)});
+    if (n > 4 * cu) shapes.push_back({512, 2 * cu});
     for (int g = std::min(n, cu); g > 0; g /= 2) shapes.push_back({1024, g});
     int choice = 0;
     if (perch_status e = ctx->ensure_first(b.icp, &choice, [&](int k) {

@@ -272,3 +272,36 @@ def test_device_tile_refinement_matches_oracle(ctx, method):
     exp = run(m, scene, starts, delta_mm=5.0, flags=0, rho_mm=10.0, iterations=5, stride=2, threads=THREADS, **kw)
     check(got, exp, f"device tile {method}")
     assert exp[2].min() > 1000 and exp[1].min() >= 1
+
+
+@pytest.mark.parametrize("method", ["point", "plane"])
+def test_either_side_of_the_work_group_sizes(ctx, method):
+    """Four poses per compute unit, the most that one work-group each refines,
+    and one more, for which two smaller ones share the unit: the results of
+    the poses a few at a time, and the oracle's on a sample."""
+    W, H = 88, 66
+    K = (W, H, 1.1 * W, 1.05 * W, W / 2 + 0.3, H / 2 - 0.4)
+    cube = box((-40, -40, -20), (40, 40, 20), n=3, rgb_seed=2)
+    d, _, _ = oracle.render(cube, pose_matrix(rot_x(2.3), (4, -6, 260)), K)
+    rng = np.random.default_rng(5)
+    d = np.where(d > 0, d + rng.integers(-3, 4, d.shape), 0).astype(np.uint16)
+    n = 4 * torch.cuda.get_device_properties(0).multi_processor_count
+    poses = np.stack([pose_matrix(rot_x(2.3 + rng.normal(0, 0.2)), np.array([4, -6, 260]) + rng.normal(0, 15, 3))
+                      for _ in range(n + 1)]).astype(np.float32)
+    say(f"icp work-group sizes: {n} and {n + 1} poses, {method}")
+    sid = ctx.set_scene(K, d, None, delta_mm=8.0, mark_occluders=False)
+    mid = ctx.load_mesh(cube.xyz, cube.tri)
+    kw = dict(rho_mm=25.0, iterations=4, stride=2, min_points=4)
+    runs = [gpu_refine(ctx, sid, mid, poses[:k], dof=6, method=method, **kw) for k in (n, n + 1)]
+    few = [gpu_refine(ctx, sid, mid, poses[k:k + 100], dof=6, method=method, **kw) for k in range(0, n + 1, 100)]
+    ctx.drop_scene(sid)
+    ctx.unload_mesh(mid)
+    for k, got in zip((n, n + 1), runs):
+        check(got, [np.concatenate([f[c] for f in few])[:k] for c in range(3)], f"{k} poses against a few at a time")
+    sel = np.r_[0:30, n - 10:n + 1]
+    if method == "point":
+        kw["dof"] = 6
+    exp = (oracle.icp if method == "point" else oracle.gicp)(cube, TScene(K, d), poses[sel], delta_mm=8.0, flags=0,
+                                                             threads=THREADS, **kw)
+    check([x[sel] for x in runs[1]], exp, f"{method} against the oracle")
+    assert exp[2].sum() > 0

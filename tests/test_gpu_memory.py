@@ -83,7 +83,7 @@ def _around(gt, n, seed):
 @pytest.mark.parametrize("method,dof", [("point", 3), ("plane", 6)])
 @pytest.mark.parametrize("megabytes", [None, 1200, 300, 60])
 def test_refinement_in_less_scratch(method, dof, megabytes):
-    """600 poses at stride 1 want 1.4 GB of scratch (GICP 2.0): with a budget
+    """1,100 poses at stride 1 want 1.4 GB of scratch (GICP 2.0): with a budget
     of less the results are the same, and a call after the first one queues
     its work without waiting for the device."""
     K, mesh, gt, d, _ = _table_top()
@@ -91,7 +91,7 @@ def test_refinement_in_less_scratch(method, dof, megabytes):
     kw = dict(rho_mm=15.0, iterations=4, stride=1, dof=dof, method=method)
     with pk.Context(0) as ctx:
         sid, mid = ctx.set_scene(K, d, delta_mm=8.0), ctx.load_mesh(mesh.xyz, mesh.tri)
-        t = _around(gt, 600, 3)
+        t = _around(gt, 1100, 3)
         ref = [x.cpu() for x in ctx.refine_poses(sid, mid, t, **kw)]
     with pk.Context(0, hbm_budget_bytes=(megabytes or 8000) << 20) as ctx:
         sid, mid = ctx.set_scene(K, d, delta_mm=8.0), ctx.load_mesh(mesh.xyz, mesh.tri)
