@@ -129,11 +129,15 @@ hipError_t launch_table_ranges(const SceneDev &s, uint32_t *tmp, int2 *thdr, lon
                                hipStream_t st);
 // Block sums the table scan needs (long long each).
 int table_scan_blocks(int n_pixels);
-// Fills the table; entries at or past `cap` are not written (a table sized
-// on the host holds exactly the count the ranges kernels reach).
-// Window offsets of the table fill: {dx, dy in 16 bits each, the whole pixels of their distance in column units}.
-constexpr int kFillOffsMax = 16384;      // 128 KB
+// Window offsets of the table fill, nearest first: {dx, dy in 16 bits each, the
+// whole pixels of their distance in column units}, and the bits of an offset's
+// raster rank.  At most kFillOffsMax (128 KB); none where the general fill has
+// to do the work.
+constexpr int kFillOffsMax = 16384;
 void table_fill_offsets(const SceneDev &s, std::vector<int2> *out, int *bits);
+// Fills the table, by the listed offsets or, with none, by the general fill;
+// entries at or past `cap` are not written (a table sized on the host holds
+// exactly the count the ranges kernels reach).
 hipError_t launch_table_fill(const SceneDev &s, const int2 *offs, int n_offs, int bits, int32_t *tnn, long long cap,
                              hipStream_t st);
 constexpr uint32_t kHashFlag = 1u << 9;   // PERCH_HASH

@@ -1,15 +1,16 @@
 // gfx950 kernels for PERCH 2.0 pose scoring.
 //
 // Per candidate pose (Sec. IV-A "Parallel Rendering" / "Parallel Cost
-// Computation", Eq. 1-4), one work-group:
+// Computation", Eq. 1-4), one work-group, or several in launches of few poses:
 //   1. rasterize the mesh into a tile of 32-bit keys (depth mm << 16 |
 //      triangle index) in LDS, min-combined with ds_min_u32;
-//   2. resolve: drop occluders (Eq. 3, C from the observed depth) and pixels
-//      off the downsampling grid;
+//   2. in one pass over the tile, drop occluders (Eq. 3, C from the observed
+//      depth) and pixels off the downsampling grid;
 //   3. J_r: each rendered point's nearest observed point within delta is one
-//      lookup in the scene's nearest-neighbour table; every inlier then
-//      marks the observed points within delta of it with its (squared
-//      distance, index) key, one wave per inlier;
+//      lookup in the scene's nearest-neighbour table (or a search, see the
+//      variants); every inlier then marks the observed points within delta of
+//      it with its (squared distance, index) key, one inlier per lane, the
+//      whole wave for one where they are few;
 //   4. J_o: an observed point inside V(O) is explained iff it was marked, and
 //      its key names its nearest rendered point;
 //   5. RGB mode: CIEDE2000 of each point against its nearest neighbour
@@ -403,6 +404,10 @@ __device__ __forceinline__ int tile_row(int k, int tw, float inv)
 
 // ------------------------------------------------------------------ per pose
 
+// Inlined by force, as score_pose_lds is.  Outlined, its arguments arrive in
+// vector registers, the loop over bands with its barriers is headed by a value
+// per lane, and two builds in which the compiler had outlined an earlier form
+// stopped responding; what in them did is not known.
 template <int BLOCK, bool G, bool KG, bool RGB, bool PV>
 __device__ __forceinline__ void score_pose(const Work &w, int p, uint32_t *tile, typename KeyOf<KG>::T *keys, float4 *labs, int *cnt,
                            int2 *wq)
@@ -497,7 +502,8 @@ __device__ __forceinline__ void score_pose(const Work &w, int p, uint32_t *tile,
 
         // 2. first band: occluders (Eq. 3) and the downsampling stride, in the
         //    same pass over the tile as phase 3 (a pass of its own: 1.11
-        //    against 1.09 ms for 6,000 nearest-neighbour poses of this class).
+        //    against 1.09 ms for 6,000 nearest-neighbour poses of this class,
+        //    inside the spread of runs; one pass is the less code).
         // 3. J_r: nearest observed neighbour from the scene table (or the
         //    kNN II scan).  Queued inliers are colour-tested (Eq. 4, first
         //    band) and mark the observed points they explain.
@@ -745,18 +751,21 @@ __device__ __forceinline__ void score_pose(const Work &w, int p, uint32_t *tile,
 // another turn might overflow it.
 template <int BLOCK> constexpr int kListCap = 8 * BLOCK;
 
-// One pose of the LDS classes (tile and J_o keys in LDS) in launches without
-// the paper's variants (whose poses, with no marking to share out, take longer
-// with the list's barriers: 1,200 nearest-neighbour poses an object, 1.20 ms
-// against 1.12).  The inliers of the
-// whole group go into one list and their colour tests and marking are shared
+// One pose of the LDS classes (tile and J_o keys in LDS) in launches whose
+// scenes are all without the paper's variants.  A nearest-neighbour pose has
+// no marking to share out and takes longer with the list's barriers (1,200
+// poses an object, 1.20 ms against 1.12); hash and kNN II poses with exact J_o,
+// whose searches are most of their time, stay with it on score_pose, as does
+// what shares a launch with such a scene: not measured here.  The inliers of
+// the whole group go into one list and their colour tests and marking are shared
 // out over its waves: full waves of 64 tests whatever the spread of the
 // inliers over the image, and every wave marking (in units of some window
 // rows of 64 inliers) until the last unit is done.  With a queue per wave a
 // flush carried 29 inliers on average, and the waves over the object's near
 // side marked while the others waited at the barrier: 32,000 poses of one
-// object with colour 13.66 -> 11.86 ms, 8,000 6-DoF poses without 6.27 ->
-// 5.99, 512 poses of a grid without 121 -> 113 us.  What bounds it now is
+// object with colour 13.66 -> 11.86 ms; 8,000 6-DoF poses without 6.27 -> 5.99
+// and 512 poses of a grid without 121 -> 113 us, both inside the spread of
+// runs.  What bounds it now is
 // vector work and LDS atomics of the marking (28-40 us of a large pose's
 // ~100), then the raster (9-15, 6-DoF 44-65) and the two window scans (16-20
 // each).

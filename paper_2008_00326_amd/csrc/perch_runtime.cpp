@@ -559,7 +559,7 @@ int wide_max_poses(const SceneDev &s)
 // us at 1024, 134 at 2048; 640x480, 256 poses of near-truth candidates 323
 // and 263).
 constexpr int kWideGroups = 1024;
-constexpr int kWideMaxBands = 32;   // one pose: 114 us at 16, 80 at 32, 73 at 64
+constexpr int kWideMaxBands = 32;   // of fewer than 32 poses (one: 114 us at 16, 80 at 32, 73 at 64)
 
 size_t align64(size_t x) { return (x + 63) & ~(size_t)63; }
 
