@@ -238,13 +238,14 @@ inline MsgState msg_state_at(void *base, size_t n, bool rgb)
     st.near = (unsigned long long *)p;
     return st;
 }
-// Append one object (mesh m at pose P) to each of n states in place, their
-// nearest points included.
+// Append one object (mesh m at pose P) to each of n states in place; their
+// nearest points are brought up to date with the last object of a series.
 struct MsgAdd {
     MeshDev m;
     MsgState st;
     const float *pose;        // 12 binary32 (device)
     uint32_t *keys;           // W*H raster keys
+    int *box;                 // bounds of the points of the series: -x0, -y0, x1, y1, least ints without any
     int label;
 };
 constexpr int kMsgAdds = 8;
@@ -252,6 +253,7 @@ struct MsgAddArgs {
     SceneDev s;
     MsgAdd add[kMsgAdds];
     int n;
+    bool first, last;         // of a series appended to the same states
     int *flag;                // set to 1 when an object occludes its state (not monotone)
 };
 // Successors of one state: one object at each of n poses.

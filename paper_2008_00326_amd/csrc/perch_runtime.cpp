@@ -1734,12 +1734,14 @@ perch_status perch_refine_poses(perch_ctx *ctx, int32_t scene_id, int32_t mesh_i
 
 namespace {
 
-// Layout of a stream's tree buffer: cursor and flag, then the raster keys of
+// Layout of a stream's tree buffer: cursor, flag and boxes, then the raster keys of
 // a composition, the placed poses, the launch's items, the per-work-group
 // tiles and the scores.
 struct MsgLayout {
     size_t keys, poses, items, tiles, out, bytes;
 };
+constexpr size_t kMsgBoxes = 320;     // of the points appended at once; the flag at 256
+static_assert(kMsgBoxes + kMsgAdds * 4 * sizeof(int) <= 512, "in the head of the buffer");
 // adds: objects appended at once (raster keys each)
 static MsgLayout msg_layout(size_t px, int grid, size_t adds, size_t n_poses, size_t n_items, size_t n_out)
 {
@@ -1854,8 +1856,10 @@ perch_status perch_msg_expand(perch_ctx *ctx, int32_t scene_id, const perch_plac
             MsgAddArgs a{};
             a.s = s;
             a.n = 1;
+            a.first = k == 0;
+            a.last = k == n_state - 1;
             a.add[0] = MsgAdd{ctx->meshes[state[k].mesh_id].dev, ms, dp + 12 * (size_t)k, (uint32_t *)(base + l.keys),
-                              state[k].label};
+                              (int *)(base + kMsgBoxes), state[k].label};
             a.flag = flag;
             HIP_TRY(msg_state_add(a, st));
         }
@@ -2030,6 +2034,7 @@ perch_status perch_msg_search(perch_ctx *ctx, int32_t scene_id, const perch_msg_
             MsgAddArgs a{};
             a.s = s;
             a.n = (int)std::min(adds, keep - c0);
+            a.first = a.last = true;
             a.flag = (int *)(base2 + 256);
             for (int k = 0; k < a.n; ++k) {
                 const Cand &cd = cand[c0 + k];
@@ -2038,7 +2043,8 @@ perch_status perch_msg_search(perch_ctx *ctx, int32_t scene_id, const perch_msg_
                                        hipMemcpyDeviceToDevice, st));
                 a.add[k] = MsgAdd{ctx->meshes[objects[cd.o].mesh_id].dev, msg_state_at(dst, px, rgb),
                                   objects[cd.o].poses_dev + 12 * (size_t)cd.k,
-                                  (uint32_t *)(base2 + l.keys + k * key_bytes), objects[cd.o].label};
+                                  (uint32_t *)(base2 + l.keys + k * key_bytes), (int *)(base2 + kMsgBoxes) + 4 * k,
+                                  objects[cd.o].label};
             }
             HIP_TRY(msg_state_add(a, st));
         }

@@ -362,3 +362,81 @@ def test_device_tile_successors_match_oracle(ctx):
             assert not exp[0].any()
     ctx.unload_mesh(mid)
     ctx.drop_scene(sid)
+
+
+def _row_of_boxes(K, z, n):
+    """Boxes side by side from the nearest to the farthest, each a little
+    behind the one before, the first and the last partly outside the image."""
+    from tiny_meshes import box, pose_matrix, rot_x
+    mesh = box((-35, -45, -30), (35, 45, 30), n=2, rgb_seed=4)
+    half = 0.5 * K[0] / K[2]
+    zs = [z + 120.0 * k for k in range(n)]                # farther than a box is deep: each state is monotone
+    return mesh, [pose_matrix(rot_x(0.3), (half * zs[k] * (2 * k / (n - 1) - 1), 10.0 * (k % 3) - 10.0, zs[k]))
+                  for k in range(n)]
+
+
+@pytest.mark.parametrize("rgb", [False, True])
+@pytest.mark.parametrize("n", [2, 7, 12])
+def test_states_of_many_objects(ctx, n, rgb):
+    """The nearest points of a state are brought up to date once for all its
+    objects: the scores of a successor beside them, for states that cover a
+    part of the image and all of it, one of whose objects adds no point."""
+    from tiny_meshes import TScene
+    K = (150, 110, 160.0, 155.0, 75.0, 55.0)
+    mesh, poses = _row_of_boxes(K, 420.0, n)
+    rng = np.random.default_rng(n)
+    depth = np.zeros((110, 150), np.int64)
+    col = np.zeros((110, 150, 3), np.uint8)
+    for P in poses[::-1]:
+        d, _, c = oracle.render(mesh, P, K)
+        depth, col = np.where(d > 0, d, depth), np.where((d > 0)[..., None], c, col)
+    depth = np.where(depth > 0, depth + rng.integers(-4, 5, depth.shape), 0).astype(np.uint16)
+    gone = poses[0].copy()
+    gone[3] += 4000.0                                     # beside the image: draws nothing
+    placed = poses[:-1][: n // 2] + [gone] + poses[:-1][n // 2:]
+    cand = np.stack([poses[-1]] * 12).astype(np.float32)
+    cand[:, [3, 7, 11]] += rng.normal(0, 6, (12, 3)).astype(np.float32)
+    flags = oracle.MARK_OCCLUDERS | (oracle.USE_RGB if rgb else 0)
+    say(f"state of {len(placed)} objects, rgb {rgb}")
+    sid = ctx.set_scene(K, depth, col, delta_mm=12.0, tau_c=20.0, flags=flags)
+    mid = ctx.load_mesh(mesh.xyz, mesh.tri, mesh.rgb)
+    got = ctx.msg_expand(sid, [(mid, 1, P) for P in placed], mid, _cuda(cand), label=2)
+    torch.cuda.synchronize()
+    exp = oracle.msg_expand(TScene(K, depth, col), [(mesh, 1, P) for P in placed], mesh, cand, label=2, delta_mm=12.0,
+                            tau_c=20.0, flags=flags, threads=THREADS)
+    check_edges(got, exp, rgb, f"{n} boxes")
+    ctx.drop_scene(sid)
+    ctx.unload_mesh(mid)
+    assert exp[0].any() and exp[4].max() > 0
+
+
+def test_time_of_a_state_does_not_grow_with_its_objects_area(ctx):
+    """A state of 24 objects, each as large as the image, at delta 30 mm takes
+    little more than one of a single such object: what an object adds is its
+    raster and composition (some 20 us), not a pass over all neighbour windows
+    (2 ms).  With such a pass for each object the two were 6.5 apart."""
+    from tiny_meshes import box, pose_matrix, rot_x
+    K = (640, 480, 525.0, 525.0, 320.0, 240.0)
+    h, z = 240, 700
+    cube = box((-h, -h, -h), (h, h, h), n=10, rgb_seed=8)
+    d, _, c = oracle.render(cube, pose_matrix(rot_x(0.5), (10, -5, z)), K)
+    d = np.where(d > 0, d, z + h + 100).astype(np.uint16)
+    sid = ctx.set_scene(K, d, c, delta_mm=30.0, tau_c=20.0)
+    mid = ctx.load_mesh(cube.xyz, cube.tri, cube.rgb)
+    ms = []
+    for n in (1, 24):
+        state = [(mid, 0, pose_matrix(rot_x(0.5), (10 + 3 * k, -5, z + 5 * h * k))) for k in range(n)]
+        t = _cuda(np.stack([pose_matrix(rot_x(0.5), (10 + k, -5, z + 5 * h * n)) for k in range(8)]))
+        times = []
+        for _ in range(7):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            ctx.msg_expand(sid, state, mid, t, label=0)
+            b.record()
+            b.synchronize()
+            times.append(a.elapsed_time(b))
+        ms.append(sorted(times)[3])
+    say(f"state of 1 object {ms[0]:.2f} ms, of 24 {ms[1]:.2f} ms")
+    ctx.drop_scene(sid)
+    ctx.unload_mesh(mid)
+    assert ms[1] < 2.5 * ms[0]
