@@ -64,8 +64,8 @@ __global__ __launch_bounds__(256) void msg_raster_kernel(MsgAddArgs a)
 // take its depth and colour, and become points of R \ C on the stride grid
 // unless the observed depth marks them as occluded (Eq. 3, the object's own
 // label exempt); a pixel where it is nearer than the state flags the state
-// as not monotone.  Observed points inside its volume become covered, and the
-// box grows to hold the new points.
+// as not monotone.  Observed points inside its volume become covered, and a
+// series' box grows to hold the new points.
 __global__ __launch_bounds__(256) void msg_compose_kernel(MsgAddArgs a)
 {
     const SceneDev &s = a.s;
@@ -114,6 +114,7 @@ __global__ __launch_bounds__(256) void msg_compose_kernel(MsgAddArgs a)
             if (in) ad.st.cov[k] = 1;
         }
     }
+    if (a.first && a.last) return;                 // a single object: its projected box will do
     if (!__syncthreads_or(b[2] >= 0)) return;      // no new point in this work-group's pixels
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
@@ -128,7 +129,9 @@ __global__ __launch_bounds__(256) void msg_compose_kernel(MsgAddArgs a)
 
 // Per observed pixel, the nearest point of the state's R \ C within delta:
 // min (squared distance << 32 | pixel), ~0 when none.  Only the objects
-// appended since the last time have new points, and compose has their box:
+// appended since the last time have new points, in the box that compose keeps
+// of a series' points or in a single object's projected box (a tree search's
+// children, where the box's reduction costs 6 % of an exhaustive search):
 // pixels beyond it grown by the scene's neighbour windows keep what they have.
 // One pass for a series of objects, on as many work-groups as the image fills
 // (640x480, all of msg_expand with a state of one object and of 32: small
@@ -140,9 +143,31 @@ __global__ __launch_bounds__(256) void msg_near_kernel(MsgAddArgs a)
     const SceneDev &s = a.s;
     const MsgAdd &ad = a.add[blockIdx.y];
     const MsgState st = ad.st;
-    if (ad.box[2] < 0) return;
-    const int x0 = max(-ad.box[0] - s.wtx, 0), y0 = max(-ad.box[1] - s.wty, 0);
-    const int x1 = min(ad.box[2] + s.wtx, s.W - 1), y1 = min(ad.box[3] + s.wty, s.H - 1);
+    int x0, y0, x1, y1;
+    if (a.first && a.last) {
+        float P[12];
+#pragma unroll
+        for (int k = 0; k < 12; ++k) P[k] = ad.pose[k];
+        double umin, umax, vmin, vmax, zmin, zmax;
+        project_box_wave(P, ad.m.lo, ad.m.hi, 0.0, s, threadIdx.x & 63, &umin, &umax, &vmin, &vmax, &zmin, &zmax);
+        int bw = s.W, bh = s.H;
+        x0 = y0 = 0;
+        if (zmin >= 100.0) clip_box(umin, umax, vmin, vmax, s.W, s.H, &x0, &y0, &bw, &bh);
+        else if (zmax < 99.999) bw = bh = 0;
+        if (bw == 0 || bh == 0) return;
+        x1 = x0 + bw - 1;
+        y1 = y0 + bh - 1;
+    } else {
+        x0 = -ad.box[0];
+        y0 = -ad.box[1];
+        x1 = ad.box[2];
+        y1 = ad.box[3];
+        if (x1 < 0) return;
+    }
+    x0 = max(x0 - s.wtx, 0);
+    y0 = max(y0 - s.wty, 0);
+    x1 = min(x1 + s.wtx, s.W - 1);
+    y1 = min(y1 + s.wty, s.H - 1);
     const int w = x1 - x0 + 1, n = w * (y1 - y0 + 1);
     const float dlw = s.delta + 0.25f, winv = 1.0f / (float)w;
     for (int q = blockIdx.x * 256 + threadIdx.x; q < n; q += gridDim.x * 256) {
@@ -551,7 +576,8 @@ hipError_t msg_state_add(const MsgAddArgs &a, hipStream_t stream)
     msg_keys_kernel<<<px, 256, 0, stream>>>(a);
     msg_raster_kernel<<<dim3((nt + 255) / 256, a.n), 256, 0, stream>>>(a);
     msg_compose_kernel<<<px, 256, 0, stream>>>(a);
-    if (a.last) msg_near_kernel<<<px, 256, 0, stream>>>(a);
+    // many states at once share the device: fewer work-groups of each, most of which a small box leaves empty
+    if (a.last) msg_near_kernel<<<dim3(a.n > 1 ? std::min(px.x, 512u) : px.x, a.n), 256, 0, stream>>>(a);
     return hipGetLastError();
 }
 
