@@ -1674,8 +1674,9 @@ perch_status perch_refine_poses(perch_ctx *ctx, int32_t scene_id, int32_t mesh_i
     // 38k, 12k and 3k pixels: 300 poses 7.7 / 9.9, 1.53 / 2.03; 512 10.4 /
     // 11.7, 2.24 / 2.35, 0.75 / 0.76; 1,024 14.8 / 16.4, 3.47 / 3.68, 1.20 /
     // 1.17; 1,280 19.1 / 20.1, 4.43 / 4.29, 1.54 / 1.42; 2,048 26.2 / 26.2, 6.62
-    // / 6.31, 2.31 / 2.03.  What holds the larger object back is its search,
-    // not its tile beyond the halved LDS (20,064 pixels: 11.8 / 12.1).
+    // / 6.31, 2.31 / 2.03; 300 of some 30 points each (stride 16) 0.29 / 0.23 at
+    // worst.  What holds the larger object back is its search, not its tile
+    // beyond the halved LDS (20,064 pixels, 2,048 poses: 11.8 / 12.1).
     const int cu = std::max(ctx->n_cu, 1);
     struct Shape {
         int block, grid;
