@@ -536,7 +536,9 @@ __device__ __noinline__ int gicp_update(const long long *z, const long long mu[3
 // 3-DoF poses against a label 25.2 -> 2.6 ms, 128 GICP poses of a 20k-triangle
 // mesh 12.6 -> 0.9 ms; before, a wave scanned the whole window of each point
 // and computed each GICP term set once per match.  Of a pose's time now: the
-// search 70 %, the sums 18 %, the raster 5 %.
+// search 70 %, the sums 18 %, the raster 5 %.  Full launches issue vector
+// instructions at 0.61-0.63 of the card's rate; 32 (GICP 42) of the 128
+// registers' worth is spilled, raster, normals, search and sums sharing them.
 template <int BLOCK, bool GICP>
 __global__ __launch_bounds__(BLOCK, 4) void icp_kernel(IcpArgs a)
 {

@@ -223,7 +223,8 @@ constexpr int kMsgBlock = 1024;
 // LDS.  All successors of a level go in one launch.  Three objects of 400
 // candidates, beam 4, 640x480 RGB: 21.8 ms in 15 launches -> 3.3 ms in 3; what
 // is left is spread over the parts (raster 14 %, its set-up 11 %, J_r 30 %,
-// J_o 35 %), each a chain of loads at 16 waves per compute unit.
+// J_o 35 %), each a chain of loads at 16 waves per compute unit (waiting 65 % of
+// their time, issue 0.53 of the card's rate; 19 registers spilled).
 template <int BLOCK>
 __global__ __launch_bounds__(BLOCK) void msg_kernel(MsgArgs a)
 {
