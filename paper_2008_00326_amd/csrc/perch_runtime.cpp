@@ -10,6 +10,7 @@
 
 #include <algorithm>
 #include <array>
+#include <chrono>
 #include <atomic>
 #include <cmath>
 #include <cstdarg>
@@ -198,7 +199,9 @@ struct perch_ctx {
     // released device blocks awaiting reuse, and recycled use-tracking events
     std::vector<CachedBlock> cache;
     size_t cached = 0;
-    size_t refused = SIZE_MAX;            // the smallest block the driver refused since memory last went back to it
+    // the smallest block the driver refused since memory last went back to it, and when
+    size_t refused = SIZE_MAX;
+    std::chrono::steady_clock::time_point refused_at{};
     std::vector<hipEvent_t> ev_pool;
 
     // profiler: HIP events around each launch, on the launch stream
@@ -328,7 +331,10 @@ struct perch_ctx {
         }
         if (e != hipSuccess) {
             reported();
-            if (e == hipErrorOutOfMemory) refused = std::min(refused, bytes);
+            if (e == hipErrorOutOfMemory) {
+                refused = std::min(refused, bytes);
+                refused_at = std::chrono::steady_clock::now();
+            }
             return fail(e == hipErrorOutOfMemory ? PERCH_ENOMEM : PERCH_EDEVICE, "hipMalloc(%zu): %s", bytes,
                         hipGetErrorString(e));
         }
@@ -363,10 +369,13 @@ struct perch_ctx {
         return alloc(b, bytes);
     }
     // Would ensure(b, bytes) succeed, as far as is known without a wait or an
-    // allocation: from the budget, and from what the driver refused before.
-    bool fits(const DevBuf &b, size_t bytes) const
+    // allocation: from the budget, and from what the driver refused within the
+    // last two seconds (others on the device may have given memory back since).
+    bool fits(const DevBuf &b, size_t bytes)
     {
         if (b.bytes >= bytes && b.ptr) return true;
+        if (refused != SIZE_MAX && std::chrono::steady_clock::now() - refused_at > std::chrono::seconds(2))
+            refused = SIZE_MAX;
         const size_t want = round_alloc(bytes == 0 ? 256 : bytes);
         return want < refused && (!budget || used - b.bytes + want <= budget);
     }
@@ -531,8 +540,10 @@ constexpr int kWideMaxPoses = 384;
 // The same for a launch with scene s in it.  Work that a band repeats for the
 // rows of its neighbours (s.wty on each side, as far as delta reaches) lowers
 // it for the paper's variants; exact J_o from the table repeats lookups only
-// (delta 40 mm, 384 poses 9547 / 3526; the least gain found is a loss, at
-// stride 2: 333 poses 291 / 291, 384 309 / 331, near candidates 317 / 274).
+// (delta 40 mm, 384 poses 9,547 / 3,526; it loses at stride 2 from 333 poses of
+// spread candidates on, 291 / 291, 384 309 / 331, near ones 317 / 274, and at
+// 1280x960 and 384 poses, 2,714 / 3,136, 200 2,118 / 1,516, while 2560x1920,
+// 384 poses takes 507,411 / 35,064).
 //   J_o by nearest-neighbour marking: the class kernels mark one bit per
 //     inlier, a band looks its neighbours' inliers up again (640x480, near
 //     candidates / spread ones: wty 13: 200 poses 138 / 117, 267 / 156; 256
