@@ -275,11 +275,13 @@ def test_device_tile_refinement_matches_oracle(ctx, method):
 
 
 @pytest.mark.parametrize("method", ["point", "plane"])
-def test_either_side_of_the_work_group_sizes(ctx, method):
+@pytest.mark.parametrize("size,rho,stride", [((88, 66), 25.0, 2), ((203, 151), 90.0, 3)])
+def test_either_side_of_the_work_group_sizes(ctx, size, rho, stride, method):
     """Four poses per compute unit, the most that one work-group each refines,
     and one more, for which two smaller ones share the unit: the results of
-    the poses a few at a time, and the oracle's on a sample."""
-    W, H = 88, 66
+    the poses a few at a time, and the oracle's on a sample; windows of one and
+    of several blocks of target tiles."""
+    W, H = size
     K = (W, H, 1.1 * W, 1.05 * W, W / 2 + 0.3, H / 2 - 0.4)
     cube = box((-40, -40, -20), (40, 40, 20), n=3, rgb_seed=2)
     d, _, _ = oracle.render(cube, pose_matrix(rot_x(2.3), (4, -6, 260)), K)
@@ -288,10 +290,10 @@ def test_either_side_of_the_work_group_sizes(ctx, method):
     n = 4 * torch.cuda.get_device_properties(0).multi_processor_count
     poses = np.stack([pose_matrix(rot_x(2.3 + rng.normal(0, 0.2)), np.array([4, -6, 260]) + rng.normal(0, 15, 3))
                       for _ in range(n + 1)]).astype(np.float32)
-    say(f"icp work-group sizes: {n} and {n + 1} poses, {method}")
+    say(f"icp work-group sizes: {n} and {n + 1} poses, {W}x{H}, {method}")
     sid = ctx.set_scene(K, d, None, delta_mm=8.0, mark_occluders=False)
     mid = ctx.load_mesh(cube.xyz, cube.tri)
-    kw = dict(rho_mm=25.0, iterations=4, stride=2, min_points=4)
+    kw = dict(rho_mm=rho, iterations=4, stride=stride, min_points=4)
     runs = [gpu_refine(ctx, sid, mid, poses[:k], dof=6, method=method, **kw) for k in (n, n + 1)]
     few = [gpu_refine(ctx, sid, mid, poses[k:k + 100], dof=6, method=method, **kw) for k in range(0, n + 1, 100)]
     ctx.drop_scene(sid)

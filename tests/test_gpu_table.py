@@ -13,7 +13,7 @@ pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
 import paper_2008_00326_amd as pk  # noqa: E402
-from tiny_meshes import TScene, box, pose_matrix, rot_x  # noqa: E402
+from tiny_meshes import box, pose_matrix, rot_x  # noqa: E402
 
 
 def say(msg):
@@ -63,6 +63,7 @@ def test_pixels_far_from_square(fy):
     """A focal length in x of millions of pixels, in y of a fraction of one:
     the table is filled without a list of offsets as long as their ratio."""
     import oracle
+    from tiny_meshes import TScene
     K = (4096, 4, 2.3e8, fy, 0.0, 2.0)
     rng = np.random.default_rng(5)
     d = rng.integers(64999, 65002, (4, 4096)).astype(np.uint16)
